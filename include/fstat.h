@@ -308,7 +308,9 @@ int fstat_detector_inputs(fstat_plan* p, const fstat_earth* earth, int32_t n_sit
  * fstat_batch_compute, 16 and 4 to 8 per thread for the 256-thread tile with
  * four waves per SIMD and FP32 coefficients, else 8 and 4),
  * waves per SIMD (interp) or SFTs per LDS chunk (direct), SFTs per
- * launch with 0 = all, work-group size of the interp kernel.  Batch classes
+ * launch with 0 = all, work-group size of the interp kernel; "1 1 0 64" leaves
+ * the choice between one wave per (sky point, spindown, 64 frequencies) and
+ * the default tile to the library, per unit, as without tuning.  Batch classes
  * ("batch_s<storage>_c<coef16>"): spindowns per thread (8: blocks of 16 and
  * 4 to 8 split per unit as fstat_batch_compute describes; 4: blocks of 4 only),
  * tiles per chunk of the per-XCD queues, SFTs per launch (0 = all), 256.
@@ -377,7 +379,9 @@ double fstat_last_kernel_ms(fstat_plan* p);
  * fstat_compute or fstat_compute_noalloc call, the last segment of
  * fstat_semicoherent, the last unit of fstat_batch_compute with the direct
  * kernel, or the last shape fstat_autotune timed; the batched interp form
- * does not set it), for tuning and tests: out[0..4] = spindowns per thread (interp) or frequencies
+ * does not set it), for tuning and tests: out[0..4] = spindowns per thread (interp; 1 with
+ * work-group size 64 and slice width 0: one wave per (sky point, spindown, 64 frequencies), the
+ * form of units too small to fill the device with tiles) or frequencies
  * per thread (direct), waves per SIMD or SFTs per LDS chunk, slice width,
  * SFTs per launch (0: all), work-group size; out[5] = slice width of the
  * tiles of two sky points (0: one sky point per tile); out[6] = number of

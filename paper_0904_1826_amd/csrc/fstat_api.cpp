@@ -628,10 +628,18 @@ Tile complete_tile(const fstat_plan* p, const fstat_wu* w, Tile t, bool paired =
   return t;
 }
 
+// The tile that stands for demod_wave_kernel (one wave per sky point,
+// spindown and 64 frequencies) in the tile map and its cache lines.
+Tile wave_tile() { return Tile{1, 1, 0, 0, 64}; }
+bool is_wave_tile(const Tile& t) { return t.nf_reg == 1 && t.chunk == 1 && t.sblock == 0 && t.threads == 64; }
+
+// The unit's tile; *is_default: no tile of its class was tuned (a class tuned
+// to the wave kernel counts as untuned: the rule picks it per unit).
 Tile pick_tile(const fstat_plan* p, const fstat_wu* w, bool* is_default = nullptr) {
   auto it = p->tiles.find(class_key(p, w));
-  if (is_default) *is_default = it == p->tiles.end();
-  return complete_tile(p, w, it != p->tiles.end() ? it->second : default_tile(p, w));
+  const bool tuned = it != p->tiles.end() && !is_wave_tile(it->second);
+  if (is_default) *is_default = !tuned;
+  return complete_tile(p, w, tuned ? it->second : default_tile(p, w));
 }
 
 int ensure_toplist(fstat_plan* p, const fstat_out* o) {
@@ -1026,6 +1034,54 @@ int prepare_pairs(fstat_plan* p, const fstat_wu* wu, WuDev& v, Tile& t, hipStrea
   }
   p->sky_staged = nullptr;
   return pair_sky(p, wu, v, t, st, default_tile_used, *p->status_h, p->sky_h, p->pairs_h, p->pairs_d);
+}
+
+// Whether demod_wave_kernel is expected to beat the interp tile `t` (already
+// completed for the unit) on this unit.  Both are modelled as time per SFT,
+// measured on 1 to 900 sky points x 1 to 40 spindowns x 1800 frequencies:
+// - the wave kernel takes 0.19 us + 2.27e-6 us per template (1.27e-6 with FP16
+//   coefficients, whose loads are half as wide): 0.30 us at 5e4 templates,
+//   1.11 at 4e5, 3.7 at 1.6e6 (4.3e11 pairs/s, the rate of its 64-byte loads);
+// - the tile kernels, however few their tiles, take the latency of a staged
+//   slice, a barrier and a thread's spindowns per SFT and launch: 1.04 us with
+//   4 per thread, 1.21 with 5, 1.29 with 6 or 7, 1.46 with 8, 2.17 with 16
+//   (FP16 coefficients 1.28 with 8), summed over the ranges of a split, whose
+//   launches follow each other; they come down to 1.05e-6 us per template.
+// So 8 spindowns cross at 5.6e5 templates (1.47 against 1.11 us at 4.0e5, 1.64
+// against 1.94 at 8.1e5), 16 at 8.7e5 and 24 = 16 + 8 at 1.5e6 (3.64 against
+// 1.96 us at 8.2e5, 3.89 against 3.71 at 1.6e6).  One or two spindowns have no
+// efficient tile (4.1 against 2.2 us at 8e5 templates x 1 spindown, 7.1 against
+// 6.7 at 2.9e6 x 2).  Units whose block of 16 spindowns outgrows the slice keep
+// the tiles: their spindowns share few cache lines.
+bool wave_beats_tile(const fstat_plan* p, const fstat_wu* wu, const Tile& t) {
+  if (resolved_kernel(p) != fstat::KERNEL_INTERP || p->force_seg > 0) return false;
+  bool fits = false;
+  (void)interp_seg(p, wu, 16, fstat::kThreads, &fits);
+  if (!fits) return false;
+  if (wu->n_fd <= 2) return true;
+  static const double kFloor[17] = {0.0,  0.0, 0.0, 0.0, 1.04, 1.21, 1.29, 1.29, 1.46,
+                                    0.0, 0.0, 0.0, 0.0, 0.0,  0.0,  0.0,  2.17};
+  double tile_us = 0.0;
+  bool split = false;
+  for (int i = 0; i < fstat::kSplitSizes; ++i) {
+    if (t.fd_split[i] <= 0) continue;
+    split = true;
+    tile_us += kFloor[fstat::split_nfd(i)];
+  }
+  if (!split) tile_us = kFloor[8];
+  if (coef16(p)) tile_us *= 1.28 / 1.46;
+  const double templates = (double)wu->n_sky * (double)wu->n_fd * (double)((wu->n_f + 63) / 64 * 64);
+  return 0.19 + (coef16(p) ? 1.27e-6 : 2.27e-6) * templates < tile_us;
+}
+
+// Turns the completed tile into the wave kernel's where the rule (for the
+// default tile) or the tuned class asks for it.
+void pick_wave(const fstat_plan* p, const fstat_wu* wu, Tile& t, bool default_tile_used) {
+  if (!default_tile_used || !wave_beats_tile(p, wu, t)) return;
+  const int32_t pair_seg = t.pair_seg;
+  t = wave_tile();
+  t.wave = 1;
+  t.pair_seg = pair_seg;             // a work-group of the wave kernel covers both points of a pair
 }
 
 // Launch shape of the batched form (a Tile under the plan's batch class):
@@ -1549,6 +1605,7 @@ int fstat_compute(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void*
   Tile t = pick_tile(p, wu, &dflt);
   rc = prepare_pairs(p, wu, v, t, st, dflt);
   if (rc) return rc;
+  pick_wave(p, wu, t, dflt);
   rc = run_demod(p, v, t, st);
   if (rc == FSTAT_OK) queue_drop_check(p, p->status_d, p->status_h, 0, st);
   return rc;
@@ -1604,8 +1661,10 @@ int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* ou
   }
   rc = run_geometry_at(p, v, status, st, -1);
   if (rc) return rc;
-  Tile t = pick_tile(p, wu);
+  bool dflt = false;
+  Tile t = pick_tile(p, wu, &dflt);
   t.sblock = 0;                      // one launch over all SFTs: no carried Fa, Fb
+  pick_wave(p, wu, t, dflt);
   rc = run_demod(p, v, t, st);
   if (rc == FSTAT_OK) queue_drop_check(p, status, p->status_h, 0, st);
   return rc;
@@ -1752,6 +1811,7 @@ int fstat_semicoherent(fstat_plan* p, const fstat_wu* segs, int32_t n_seg, const
                     p->pairs_h + (size_t)n * k, p->pairs_d + (size_t)n * k);
       if (rc) return rc;
     }
+    pick_wave(p, &segs[k], t, dflt);
     rc = run_demod(p, v, t, st, p->seg_ev[2 * (size_t)k], p->seg_ev[2 * (size_t)k + 1]);
     if (rc) return rc;
   }
@@ -1791,6 +1851,7 @@ static_assert(FSTAT_NOALLOC_SCRATCH_BYTES == fstat::kStaticScratchBytes, "one si
 static bool valid_tile(const fstat_plan* p, const Tile& t) {
   if (t.sblock < 0) return false;
   if (resolved_kernel(p) == fstat::KERNEL_INTERP) {
+    if (is_wave_tile(t)) return true;
     const bool nf_ok = t.nf_reg == 8 || t.nf_reg == 4 || t.nf_reg == 2 || t.nf_reg == 1;
     // 4 (FP16 coefficients: 4 or 5) waves per SIMD: 256-thread tiles with 8 spindowns per thread
     const bool wide = t.nf_reg == 8 && t.threads == 256 && (t.chunk == 4 || (t.chunk == 5 && coef16(p)));
@@ -1902,16 +1963,19 @@ int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void
               const Tile t{nfd, minw, 0, sb, nt};
               if ((nfd <= 2 * wu->n_fd || nfd == 1) && (nfd == 8 || minw == 3) && valid_tile(p, t)) cands.push_back(t);
             }
+      if (wave_beats_tile(p, wu, complete_tile(p, wu, default_tile(p, wu)))) cands.push_back(wave_tile());
     } else {
       cands = {Tile{1, 16, 0, 0, 0}, Tile{1, 8, 0, 0, 0}, Tile{2, 8, 0, 0, 0}, Tile{2, 4, 0, 0, 0}, Tile{4, 4, 0, 0, 0}};
     }
     float best = 1e30f;
     Tile best_t = default_tile(p, wu);
     for (Tile t0 : cands) {
-      Tile t = complete_tile(p, wu, t0);            // as pick_tile and fstat_compute run it
+      const bool wave = interp && is_wave_tile(t0);
+      Tile t = complete_tile(p, wu, wave ? default_tile(p, wu) : t0);   // as pick_tile and fstat_compute run it
       WuDev vt = v;
-      rc = prepare_pairs(p, wu, vt, t, st, false);
+      rc = prepare_pairs(p, wu, vt, t, st, wave);
       if (rc) return rc;
+      pick_wave(p, wu, t, wave);
       float ms = 0.f;
       for (int rep = 0; rep < 2; ++rep) {
         rc = run_demod(p, vt, t, st);

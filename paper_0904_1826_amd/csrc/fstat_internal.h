@@ -76,6 +76,7 @@ struct Tile {
   // all zero: one range of nf_reg per thread with slice width seg
   int32_t fd_split[kSplitSizes];
   int32_t seg_split[kSplitSizes];
+  int32_t wave;     // interp: 1: one wave per (sky point, spindown, 64 frequencies), no LDS slice (demod_wave_kernel)
 };
 
 enum Kernel : int32_t { KERNEL_DIRECT = 1, KERNEL_INTERP = 2 };

@@ -1129,6 +1129,166 @@ __global__ __launch_bounds__(kThreads, batch_minw(NFD, C16, NSKY)) void demod_in
   }
 }
 
+// ------------------------------------------------ one wave per template row
+// Demodulation of work units too small to fill the device with interp tiles:
+// one wave per (sky point, spindown, 64 frequencies), one pair per lane and
+// SFT, coefficients read straight from global memory into registers.  What
+// bounds such a unit is the chain of SFTs of a tile (2.1 us per SFT with 16
+// spindowns per thread, of which most is the latency of the staged slice and
+// the barrier), not the vector units, so the wave keeps no LDS slice and no
+// barrier: it loads the coefficients of kAhead SFTs at once while it evaluates
+// the kAhead before them.  The four waves of a work-group take neighbouring
+// spindowns (with w.sky_pairs, two spindowns of each point of a pair) at the
+// same frequencies, whose coefficients share cache lines.  Per template and
+// SFT the arithmetic is that of interp_tile, in the same order, so the results
+// are the same bit for bit.  1 sky point x 51 spindowns x 1801 frequencies x
+// 1500 SFTs: 4.75 ms in tiles (32 work-groups on 256 CUs), 0.48 ms here (0.32
+// us per SFT); 12 x 4 x 700 x 48: 55 and 19 us.  Larger units are bound by the
+// 64 bytes per pair through the vector cache (4.3e11 pairs/s, against 9e11 for
+// full tiles): the host picks per unit.
+constexpr int kAhead = 4;
+
+// Per-SFT values of one (sky point, spindown), formed by one lane per SFT.
+struct WaveSft {
+  double tau, p, q;         // tau, Tdot T, (fdot tau) Tdot T
+  float2 tsplit;            // tau as hi + lo FP32 (split phase mode)
+  float2 e;                 // exp(-2 pi i frac(tau (fdot/2) tau))
+  float a, b;
+};
+
+__host__ __device__ constexpr int wave_spindowns(bool pairs, int64_t n_fd) {
+  return pairs ? 2 : n_fd >= 3 ? 4 : (int)n_fd;
+}
+
+template <bool C16>
+__global__ __launch_bounds__(kThreads, 3) void demod_wave_kernel(WuDev w) {
+  __shared__ WaveSft lds[kThreads / 64][128];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const bool pairs = w.n_pairs > 0;
+  const int64_t n_st = pairs ? w.n_pairs : w.n_sky;
+  // spindowns per work-group; the other factor of its four waves is the two
+  // points of a pair, or neighbouring blocks of 64 frequencies
+  const int per = wave_spindowns(pairs, w.n_fd);
+  const int64_t n_fdb = (w.n_fd + per - 1) / per;
+  int64_t t = blockIdx.x;
+  const int64_t st = t % n_st;
+  t /= n_st;
+  const int64_t i = (t % n_fdb) * per + wv % per;
+  const int64_t j0 = pairs ? (t / n_fdb) * 64 : (t / n_fdb) * (256 / per) + 64 * (wv / per);
+  int64_t s = st;
+  bool own = true;                                 // a sky point without a partner is written once
+  if (pairs) {
+    const int2 pr = w.sky_pairs[st];
+    s = wv & 2 ? pr.y : pr.x;
+    own = !(wv & 2) || pr.x != pr.y;
+  }
+  if (i >= w.n_fd || j0 >= w.n_f || !own) return;  // no barrier follows
+  const int64_t j = j0 + lane < w.n_f ? j0 + lane : w.n_f - 1;
+  const double f = template_f(w, j), fd = template_fd(w, i);
+  const float2 fsplit = split64(f);
+  const bool split_phase = w.phase_mode != 0;
+  const double2* geo = w.geo + s * w.n_sft;
+  const float* arow = w.a + s * w.n_sft;
+  const float* brow = w.b + s * w.n_sft;
+  const int n = (int)w.n_sft, k_first = (int)w.k_first, nb = (int)w.n_bins;
+  constexpr int ROWS = C16 ? kRows16 : kCoefPairs;
+  typedef typename std::conditional<C16, CoefSet16, CoefSet>::type Set;
+  WaveSft* my = lds[wv];
+
+  double2 g_next;
+  float a_next, b_next;
+  auto fetch = [&](int al0) __attribute__((always_inline)) {      // lane l: the values of SFT al0 + l
+    const int al = al0 + lane < n ? al0 + lane : n - 1;
+    g_next = geo[al];
+    const float sa = C16 ? ldexpf(1.f, w.cexp[al]) : 1.f;         // the FP16 form stores c 2^-e
+    a_next = C16 ? arow[al] * sa : arow[al];
+    b_next = C16 ? brow[al] * sa : brow[al];
+  };
+  auto publish = [&](int al0) __attribute__((always_inline)) {
+    const double2 g = g_next;
+    WaveSft x;
+    x.tau = g.x;
+    x.p = g.y;
+    x.q = bin_offset(fd, g.x, g.y);
+    x.tsplit = split64(g.x);
+    const double h = (0.5 * fd) * g.x;
+    const float ph = split_phase ? frac_split_product(split64(g.x), split64(h)) : (float)fract64(g.x * h);
+    x.e = make_float2(cos_rev(ph), -sin_rev(ph));
+    x.a = a_next;
+    x.b = b_next;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    my[(al0 + lane) & 127] = x;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  };
+
+  // coefficients and kappa of SFTs [al, al + kAhead)
+  struct Group {
+    Set c[kAhead];
+    float kap[kAhead];
+  };
+  auto load = [&](int al0, Group& g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int y = 0; y < kAhead; ++y) {
+      const int al = al0 + y < n ? al0 + y : n - 1;
+      const WaveSft& x = my[al & 127];
+      const double dphi = bin_position(f, x.q, x.p);
+      int col = (int)dphi - k_first;
+      col = col < 0 ? 0 : (col >= nb ? nb - 1 : col);             // memory safety only
+      g.kap[y] = (float)fract64(dphi);
+      const int64_t base = (int64_t)al * ROWS * nb + col;
+#pragma unroll
+      for (int q = 0; q < ROWS; ++q) {
+        if constexpr (C16) g.c[y].c[q] = reinterpret_cast<const v4f*>(w.coef)[base + (int64_t)q * nb];
+        else g.c[y].c[q] = w.coef[base + (int64_t)q * nb];
+      }
+    }
+  };
+  float far = 0.f, fai = 0.f, fbr = 0.f, fbi = 0.f;
+  auto add = [&](int al0, const Group& g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int y = 0; y < kAhead; ++y) {
+      if (al0 + y >= n) break;
+      const WaveSft& x = my[(al0 + y) & 127];
+      const float pf = split_phase ? frac_split_product(x.tsplit, fsplit) : (float)fract64(x.tau * f);
+      const float cf = cos_rev(pf), sf = sin_rev(pf);
+      if constexpr (C16)
+        interp_accumulate16(g.c[y].c[0], g.c[y].c[1], g.kap[y], cf, sf, x.e, x.a, x.b, far, fai, fbr, fbi);
+      else
+        interp_accumulate(g.c[y].c[0], g.c[y].c[1], g.c[y].c[2], g.c[y].c[3], g.kap[y], cf, sf, x.e, x.a, x.b, far,
+                          fai, fbr, fbi);
+    }
+  };
+  // the values of 64 SFTs at a time go to LDS, one block ahead; the groups
+  // alternate between two register sets
+  static_assert(64 % (2 * kAhead) == 0, "a block holds whole pairs of groups");
+  fetch(0);
+  publish(0);
+  if (n > 64) fetch(64);
+  Group ga, gb;
+  load(0, ga);
+  for (int al = 0; al < n; al += 2 * kAhead) {
+    if ((al & 63) == 0 && al + 64 < n) {
+      publish(al + 64);
+      if (al + 128 < n) fetch(al + 128);
+    }
+    if (al + kAhead < n) load(al + kAhead, gb);
+    add(al, ga);
+    if (al + 2 * kAhead < n) load(al + 2 * kAhead, ga);
+    if (al + kAhead < n) add(al + kAhead, gb);
+  }
+  if (j0 + lane >= w.n_f) return;
+  const int64_t o = (s * w.n_fd + i) * w.n_f + j;
+  const double4 abcd = w.abcd[s];
+  const double ar = far, ai = fai, br = fbr, bi = fbi;
+  const double fa2 = ar * ar + ai * ai, fb2 = br * br + bi * bi, re = ar * br + ai * bi;
+  const double two_f = 2.0 * (abcd.y * fa2 + abcd.x * fb2 - 2.0 * abcd.z * re) / abcd.w;
+  if (w.twoF) w.twoF[o] = w.accumulate ? w.twoF[o] + (float)two_f : (float)two_f;
+  if (w.cand) cand_push(w, (float)two_f, o);
+  if (w.fa) w.fa[o] = make_float2(far, fai);
+  if (w.fb) w.fb[o] = make_float2(fbr, fbi);
+}
+
 // ------------------------------------------------------------ toplist
 // Candidates of a 2F array already in memory (the semi-coherent sum): one
 // thread per template.
@@ -1534,6 +1694,21 @@ static hipError_t launch_interp(const WuDev& w, const Tile& t, hipStream_t st) {
   return hipSuccess;
 }
 
+// One wave per (sky point, spindown, 64 frequencies), t.wave set.
+static hipError_t launch_wave(const WuDev& w, hipStream_t st) {
+  const bool pairs = w.n_pairs > 0;
+  const int per = wave_spindowns(pairs, w.n_fd);
+  const int64_t nf = pairs ? 64 : 256 / per;       // frequencies per work-group
+  const int64_t blocks =
+      ((w.n_f + nf - 1) / nf) * ((w.n_fd + per - 1) / per) * (pairs ? w.n_pairs : w.n_sky);
+  if (blocks <= 0 || blocks > 0x7fffffffLL || (w.n_pairs > 0 && !w.sky_pairs)) return hipErrorInvalidConfiguration;
+  if (w.coef16)
+    hipLaunchKernelGGL(demod_wave_kernel<true>, dim3((unsigned)blocks), dim3(kThreads), 0, st, w);
+  else
+    hipLaunchKernelGGL(demod_wave_kernel<false>, dim3((unsigned)blocks), dim3(kThreads), 0, st, w);
+  return hipGetLastError();
+}
+
 template <class Seg>
 static hipError_t top_select(const Seg& seg, int n_seg, uint4* cand, int64_t cap, int max_top_k, hipStream_t st) {
   const int64_t total = (int64_t)n_seg * cap;
@@ -1594,7 +1769,7 @@ static hipError_t launch_direct_d(const WuDev& w, const Tile& t, hipStream_t st)
 }
 
 hipError_t launch_demod(const WuDev& w, const Tile& t, int kernel, hipStream_t st) {
-  if (kernel == KERNEL_INTERP) return launch_interp(w, t, st);
+  if (kernel == KERNEL_INTERP) return t.wave ? launch_wave(w, st) : launch_interp(w, t, st);
   switch (w.dterms) {
     case 8: return launch_direct_d<8>(w, t, st);
     case 16: return launch_direct_d<16>(w, t, st);
