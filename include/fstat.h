@@ -196,9 +196,10 @@ int fstat_plan_create(fstat_plan** out, const fstat_desc* d);
  * SFT sums inside.  Validates arguments on the host, then enqueues on
  * `stream`: (1) per (sky, SFT) geometry tau, Tdot and per-sky A, B, C with a
  * check that every window [k*-D+1, k*+D] of the grid lies in the band; the
- * call waits for this check and returns FSTAT_E_BAND (nothing else
- * launched) if it fails; (2) the demodulation kernel, which writes `out`
- * asynchronously.  Between the two, the interp kernel's host side copies the
+ * call waits for this check and returns FSTAT_E_BAND (no output written: at
+ * most the coefficient pass, into the plan's scratch, and a demodulation that
+ * finds the check failed and ends were queued) if it fails; (2) the
+ * demodulation kernel, which writes `out` asynchronously.  Between the two, the interp kernel's host side copies the
  * sky vectors back (one more short wait) to pair neighbouring sky points
  * into tiles of two where the slice can hold both (fstat_last_tile reports
  * the shape that ran).  Returns after (2) is enqueued. */

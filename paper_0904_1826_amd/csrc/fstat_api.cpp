@@ -34,6 +34,7 @@ struct fstat_plan {
   fstat::GeoStatus* status_h = nullptr;  // pinned
   double max_abs_tau = 0.0;               // from the last geometry pass
   double max_p = 0.0;                     // max Tdot T, from the last geometry pass
+  bool fits16 = false;                    // a block of 16 spindowns fits the slice, from the last geometry pass
   // interp kernel: coefficient scratch and per-Dterms polynomial tables
   void* coef = nullptr;
   size_t coef_bytes = 0;
@@ -117,6 +118,12 @@ struct fstat_plan {
   hipEvent_t ev_drop = nullptr;
   bool drop_pending = false;
   int drop_units = 0;
+  // the geometry pass's completion (its result is then in status_h); the
+  // stream of the plan's last call and the event after its last launch, for
+  // which a call on another stream waits before it reuses the plan's scratch
+  hipEvent_t ev_geo = nullptr;
+  hipStream_t last_stream = nullptr;
+  hipEvent_t last_event = nullptr;
 };
 
 namespace {
@@ -173,7 +180,8 @@ int check_launch(fstat_plan* p, hipError_t e, const char* what) {
 
 // The previous call's tiles that met an SFT outside their slice, once the copy has landed:
 // an error naming them (their templates' outputs are NaN), else FSTAT_OK.
-int check_prev_drops(fstat_plan* p) {
+int check_prev_drops(fstat_plan* p, hipStream_t st) {
+  if (p->last_event && st != p->last_stream) (void)hipEventSynchronize(p->last_event);
   if (!p->drop_pending) return FSTAT_OK;
   p->drop_pending = false;
   if (hipEventSynchronize(p->ev_drop) != hipSuccess) return set_err(p, FSTAT_E_DEVICE, "previous call did not complete");
@@ -211,11 +219,27 @@ void queue_drop_check(fstat_plan* p, fstat::GeoStatus* src_d, fstat::GeoStatus* 
   }
   p->drop_pending = true;
   p->drop_units = n_units;
+  p->last_stream = st;
+  p->last_event = p->ev_drop;
 }
 
 // Resets the drop counter of a single-unit call.
 int reset_drops(fstat_plan* p, fstat::GeoStatus* status_d, hipStream_t st) {
   return check_launch(p, fstat::launch_fill_int((int*)&status_d->dropped, 0, 2, st), "status reset");
+}
+
+// Only the interp kernels without the global-memory path can drop tiles.
+bool may_drop(int kernel, const Tile& t) { return kernel == fstat::KERNEL_INTERP && !t.wave && t.fast; }
+
+// The end of a single-unit call: the drop count of a launch that may drop
+// tiles goes to the host; otherwise only the call's end is marked (a wave
+// launch that nothing follows carries ev1 itself).
+void end_call(fstat_plan* p, const Tile& t, int kernel, bool toplist, fstat::GeoStatus* status_d, hipStream_t st) {
+  if (may_drop(kernel, t)) return queue_drop_check(p, status_d, p->status_h, 0, st);
+  p->last_stream = st;
+  p->last_event = p->ev1;
+  if (kernel == fstat::KERNEL_INTERP && t.wave && !toplist) return;
+  p->last_event = hipEventRecord(p->ev_drop, st) == hipSuccess ? p->ev_drop : nullptr;
 }
 
 bool finite(double x) { return std::isfinite(x); }
@@ -669,56 +693,95 @@ int ensure_scratch(fstat_plan* p, const fstat_wu* w) {
   return rc;
 }
 
-int stage_sky(fstat_plan* p, const fstat_wu* wu, hipStream_t st);
+int stage_sky(fstat_plan* p, const fstat_wu* wu, bool copy, hipStream_t st);
 
-// Geometry + band check into the status record status_d; waits for the
-// check.  With `stage` (a unit whose sky points may be paired) the host copy
-// of its sky vectors rides on the same wait.  Returns FSTAT_OK or an error.
-int run_geometry_at(fstat_plan* p, const WuDev& v, fstat::GeoStatus* status_d, hipStream_t st, int idx,
-                    const fstat_wu* stage = nullptr) {
-  p->sky_staged = nullptr;
-  int rc = check_launch(p, fstat::launch_fill_int((int*)status_d, 0, fstat::kGeoResetInts, st), "status reset");
-  if (rc) return rc;
-  rc = check_launch(p, fstat::launch_geometry(v, status_d, st), "geometry kernel");
-  if (rc) return rc;
-  hipError_t e = hipMemcpyAsync(p->status_h, status_d, sizeof(fstat::GeoStatus), hipMemcpyDeviceToHost, st);
-  if (e != hipSuccess) return hip_err(p, e, "status copy");
-  if (stage) {
-    rc = stage_sky(p, stage, st);
+// The interp kernels' coefficients.
+int run_coef(fstat_plan* p, const WuDev& v, hipStream_t st) {
+  if (v.coef16) {
+    int rc = check_launch(p, fstat::launch_cexp(v, st), "coefficient exponent kernel");
     if (rc) return rc;
   }
-  e = hipStreamSynchronize(st);
-  if (e != hipSuccess) return hip_err(p, e, "geometry kernel");
-  const int st_bits = p->status_h->flags;
-  unsigned long long tb = p->status_h->max_abs_tau_bits;
-  memcpy(&p->max_abs_tau, &tb, sizeof tb);
-  tb = p->status_h->max_p_bits;
-  memcpy(&p->max_p, &tb, sizeof tb);
-  char tag[32] = "";
-  if (idx >= 0) snprintf(tag, sizeof tag, "work unit %d: ", idx);
-  if (st_bits & 1) return set_err(p, FSTAT_E_BAND, "%sa Dirichlet window [k*-D+1, k*+D] leaves the stored band", tag);
-  if (st_bits & 2) return set_err(p, FSTAT_E_ARG, "%santenna-pattern matrix is singular (A B - C^2 <= 0)", tag);
+  return check_launch(p, fstat::launch_coef(v, st), "coefficient kernel");
+}
+
+// Sky grids up to this size ride on the geometry pass's own stores to pinned
+// memory; larger ones are copied.
+constexpr int64_t kSkyByKernel = 65536;
+
+double status_bits(unsigned long long b) {
+  double t;
+  memcpy(&t, &b, sizeof t);
+  return t;
+}
+
+// Reads the geometry pass's result of one unit from the host record.
+int read_geometry(fstat_plan* p, const fstat::GeoStatus& g, const char* tag) {
+  p->max_abs_tau = status_bits(g.max_abs_tau_bits);
+  p->max_p = status_bits(g.max_p_bits);
+  p->fits16 = (g.flags & fstat::kGeoFits16) != 0;
+  if (g.flags & 1) return set_err(p, FSTAT_E_BAND, "%sa Dirichlet window [k*-D+1, k*+D] leaves the stored band", tag);
+  if (g.flags & 2) return set_err(p, FSTAT_E_ARG, "%santenna-pattern matrix is singular (A B - C^2 <= 0)", tag);
   return FSTAT_OK;
 }
 
-int run_geometry(fstat_plan* p, const WuDev& v, hipStream_t st, int idx, const fstat_wu* stage = nullptr) {
-  return run_geometry_at(p, v, p->status_d, st, idx, stage);
+// Up to this many blocks the geometry and coefficient passes share a launch
+// (14 us of coefficients); beyond, the host reads the check while the
+// coefficient pass runs.
+constexpr int64_t kFrontBlocks = 4096;
+
+// Enqueues the geometry + band check with the status record status_d; its
+// result is in status_h once ev_geo has fired.  With `stage` (a unit whose sky
+// points may be paired) the sky vectors go to the host with it.  With `coef`
+// the coefficient passes, which do not depend on the check and write only
+// scratch, are queued too, so that the device works while the host waits.
+int queue_geometry(fstat_plan* p, const WuDev& v, fstat::GeoStatus* status_d, hipStream_t st, const fstat_wu* stage,
+                   bool coef) {
+  p->sky_staged = nullptr;
+  const bool by_kernel = stage && stage->n_sky <= kSkyByKernel;
+  int rc = by_kernel ? stage_sky(p, stage, false, st) : FSTAT_OK;
+  if (rc) return rc;
+  const bool copy = stage && !by_kernel;
+  double* sky = by_kernel ? p->sky_h : nullptr;
+  hipEvent_t done = copy ? nullptr : p->ev_geo;
+  const bool front = coef && !v.coef16 && v.n_sky <= 256 && fstat::coef_blocks(v) <= kFrontBlocks;
+  rc = check_launch(p, front ? fstat::launch_front(v, status_d, p->status_h, sky, st, done)
+                             : fstat::launch_geometry(v, status_d, p->status_h, sky, st, done),
+                    "geometry kernel");
+  if (rc) return rc;
+  // the two passes of one launch are two steps to the fault injection
+  if (front && (rc = check_launch(p, hipSuccess, "coefficient kernel"))) return rc;
+  if (copy) {
+    rc = stage_sky(p, stage, true, st);
+    if (rc) return rc;
+    const hipError_t e = hipEventRecord(p->ev_geo, st);
+    if (e != hipSuccess) return hip_err(p, e, "geometry event");
+  }
+  return coef && !front ? run_coef(p, v, st) : FSTAT_OK;
 }
 
-// `e0`, `e1`: the events around the demodulation launches (default: the
-// plan's ev0, ev1, which fstat_last_kernel_ms reads).
-int run_demod(fstat_plan* p, const WuDev& v, const Tile& t, hipStream_t st, hipEvent_t e0 = nullptr,
+// Waits for the check queued by queue_geometry.  FSTAT_OK or an error.
+int wait_geometry(fstat_plan* p, int idx) {
+  const hipError_t e = hipEventSynchronize(p->ev_geo);
+  if (e != hipSuccess) return hip_err(p, e, "geometry kernel");
+  char tag[32] = "";
+  if (idx >= 0) snprintf(tag, sizeof tag, "work unit %d: ", idx);
+  return read_geometry(p, *p->status_h, tag);
+}
+
+int run_geometry(fstat_plan* p, const WuDev& v, hipStream_t st, int idx) {
+  const int rc = queue_geometry(p, v, p->status_d, st, nullptr, false);
+  return rc ? rc : wait_geometry(p, idx);
+}
+
+// With coef_done the coefficient passes are already queued.
+int run_demod(fstat_plan* p, const WuDev& v, const Tile& t, hipStream_t st, bool coef_done, hipEvent_t e0 = nullptr,
               hipEvent_t e1 = nullptr) {
   const int kernel = resolved_kernel(p);
-  p->have_last = true;
+  p->have_last = true;                 // (a launch that its gate ends is reported too)
   p->last_tile = t;
   p->last_sky_tiles = v.n_pairs > 0 && t.pair_seg > 0 ? v.n_pairs : v.n_sky;
-  if (kernel == fstat::KERNEL_INTERP) {
-    if (v.coef16) {
-      int rc = check_launch(p, fstat::launch_cexp(v, st), "coefficient exponent kernel");
-      if (rc) return rc;
-    }
-    int rc = check_launch(p, fstat::launch_coef(v, st), "coefficient kernel");
+  if (kernel == fstat::KERNEL_INTERP && !coef_done) {
+    int rc = run_coef(p, v, st);
     if (rc) return rc;
   }
   if (v.cand) {
@@ -726,12 +789,21 @@ int run_demod(fstat_plan* p, const WuDev& v, const Tile& t, hipStream_t st, hipE
     if (rc) return rc;
   }
   const bool own = e0 == nullptr;
-  (void)hipEventRecord(own ? p->ev0 : e0, st);
-  int rc = check_launch(p, fstat::launch_demod(v, t, kernel, st), "demodulation kernel");
-  (void)hipEventRecord(own ? p->ev1 : e1, st);
+  int rc = check_launch(p, fstat::launch_demod(v, t, kernel, st, own ? p->ev0 : e0, own ? p->ev1 : e1),
+                        "demodulation kernel");
   p->ev_stream = st;
   if (own) p->timed = (rc == FSTAT_OK);
   if (rc == FSTAT_OK && v.cand) rc = check_launch(p, fstat::launch_top_select(v, st), "toplist selection");
+  return rc;
+}
+
+// The wave kernel queued behind the geometry pass, gated by its result.
+int queue_wave_ahead(fstat_plan* p, WuDev v, fstat::GeoStatus* status_d, hipStream_t st) {
+  Tile t = wave_tile();
+  t.wave = 1;
+  v.gate = &status_d->gate;
+  const int rc = run_demod(p, v, t, st, true);
+  if (rc == FSTAT_OK) end_call(p, t, fstat::KERNEL_INTERP, false, status_d, st);
   return rc;
 }
 
@@ -772,6 +844,9 @@ int ensure_pinned_pair(fstat_plan* p, T** dev, T** host, size_t* cap, size_t nee
     (void)hipGetLastError();
     return set_err(p, FSTAT_E_NOMEM, "%s: allocation of %zu entries failed", what, need);
   }
+  // status records are zero between geometry passes
+  if (hipMemset(*dev, 0, need * sizeof(T)) != hipSuccess || hipDeviceSynchronize() != hipSuccess)
+    return set_err(p, FSTAT_E_DEVICE, "%s: clearing failed", what);
   *cap = need;
   return FSTAT_OK;
 }
@@ -785,16 +860,11 @@ int batch_check(fstat_plan* p, const fstat_wu* wus, const fstat_out* outs, int k
     const WuScratch sc = wu_scratch(p, &wus[k], 0);   // geometry and A,B,C,D come first either way
     v.geo = (double2*)(geo_base + offs[k]);
     v.abcd = (double4*)(geo_base + offs[k] + sc.geo);
-    int rc = check_launch(p, fstat::launch_fill_int((int*)(p->bstat_d + k), 0, sizeof(fstat::GeoStatus) / sizeof(int), st),
-                          "status reset");
-    if (rc) return rc;
-    rc = check_launch(p, fstat::launch_geometry(v, p->bstat_d + k, st), "geometry kernel");
+    int rc = check_launch(p, fstat::launch_geometry(v, p->bstat_d + k, p->bstat_h + k, nullptr, st, nullptr),
+                          "geometry kernel");
     if (rc) return rc;
   }
-  hipError_t e = hipMemcpyAsync(p->bstat_h + k0, p->bstat_d + k0, (size_t)(k1 - k0) * sizeof(fstat::GeoStatus),
-                                hipMemcpyDeviceToHost, st);
-  if (e != hipSuccess) return hip_err(p, e, "status copy");
-  e = hipStreamSynchronize(st);
+  hipError_t e = hipStreamSynchronize(st);
   if (e != hipSuccess) return hip_err(p, e, "geometry kernel");
   for (int k = k0; k < k1; ++k) {
     const int f = p->bstat_h[k].flags;
@@ -813,12 +883,6 @@ double status_tau(const fstat::GeoStatus& g) {
 double status_p(const fstat::GeoStatus& g) {
   double t;
   memcpy(&t, &g.max_p_bits, sizeof t);
-  return t;
-}
-
-double status_bits(unsigned long long b) {
-  double t;
-  memcpy(&t, &b, sizeof t);
   return t;
 }
 
@@ -948,10 +1012,10 @@ int make_pairs(const fstat_wu* wu, const fstat::GeoStatus& g, const double* sk, 
   return (int)width & ~3;
 }
 
-// Enqueues the host copy of the unit's sky vectors into sky_h (pinned, grown
-// as needed) on st; sky_staged names the array once the stream has been
-// waited for.
-int stage_sky(fstat_plan* p, const fstat_wu* wu, hipStream_t st) {
+// Makes room for the unit's sky vectors in sky_h (pinned, grown as needed)
+// and, with `copy`, enqueues their copy on st; sky_staged names the array once
+// the geometry pass that stores them, or the copy, has been waited for.
+int stage_sky(fstat_plan* p, const fstat_wu* wu, bool copy, hipStream_t st) {
   const int64_t n = wu->n_sky;
   p->sky_staged = nullptr;
   if (p->sky_h_cap < (size_t)(3 * n)) {
@@ -964,8 +1028,11 @@ int stage_sky(fstat_plan* p, const fstat_wu* wu, hipStream_t st) {
     }
     p->sky_h_cap = (size_t)(3 * n);
   }
-  const hipError_t e = hipMemcpyAsync(p->sky_h, wu->sky, (size_t)(3 * n) * sizeof(double), hipMemcpyDeviceToHost, st);
-  if (e != hipSuccess) return hip_err(p, e, "sky vector copy");
+  if (copy) {
+    const hipError_t e =
+        hipMemcpyAsync(p->sky_h, wu->sky, (size_t)(3 * n) * sizeof(double), hipMemcpyDeviceToHost, st);
+    if (e != hipSuccess) return hip_err(p, e, "sky vector copy");
+  }
   p->sky_staged = wu->sky;
   return FSTAT_OK;
 }
@@ -1027,7 +1094,7 @@ int prepare_pairs(fstat_plan* p, const fstat_wu* wu, WuDev& v, Tile& t, hipStrea
   int rc = ensure_pinned_pair(p, &p->pairs_d, &p->pairs_h, &p->pairs_cap, (size_t)wu->n_sky, "sky pairs");
   if (rc) return rc;
   if (p->sky_staged != wu->sky) {          // not brought by this call's geometry wait
-    rc = stage_sky(p, wu, st);
+    rc = stage_sky(p, wu, true, st);
     if (rc) return rc;
     const hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_err(p, e, "sky vector copy");
@@ -1053,22 +1120,15 @@ int prepare_pairs(fstat_plan* p, const fstat_wu* wu, WuDev& v, Tile& t, hipStrea
 // efficient tile (4.1 against 2.2 us at 8e5 templates x 1 spindown, 7.1 against
 // 6.7 at 2.9e6 x 2).  Units whose block of 16 spindowns outgrows the slice keep
 // the tiles: their spindowns share few cache lines.
-bool wave_beats_tile(const fstat_plan* p, const fstat_wu* wu, const Tile& t) {
+bool wave_beats_tile(const fstat_plan* p, const fstat_wu* wu, bool paired) {
   if (resolved_kernel(p) != fstat::KERNEL_INTERP || p->force_seg > 0) return false;
-  bool fits = false;
-  (void)interp_seg(p, wu, 16, fstat::kThreads, &fits);
-  if (!fits) return false;
   if (wu->n_fd <= 2) return true;
   static const double kFloor[17] = {0.0,  0.0, 0.0, 0.0, 1.04, 1.21, 1.29, 1.29, 1.46,
                                     0.0, 0.0, 0.0, 0.0, 0.0,  0.0,  0.0,  2.17};
+  const FdSplit sp = split_spindowns(wu->n_fd, coef16(p) ? (1u << 8) | (1u << 4) : kAllSplitSizes, paired);
   double tile_us = 0.0;
-  bool split = false;
-  for (int i = 0; i < fstat::kSplitSizes; ++i) {
-    if (t.fd_split[i] <= 0) continue;
-    split = true;
-    tile_us += kFloor[fstat::split_nfd(i)];
-  }
-  if (!split) tile_us = kFloor[8];
+  for (int i = 0; i < fstat::kSplitSizes; ++i)
+    if (sp.n[i] > 0) tile_us += kFloor[fstat::split_nfd(i)];
   if (coef16(p)) tile_us *= 1.28 / 1.46;
   const double templates = (double)wu->n_sky * (double)wu->n_fd * (double)((wu->n_f + 63) / 64 * 64);
   return 0.19 + (coef16(p) ? 1.27e-6 : 2.27e-6) * templates < tile_us;
@@ -1077,11 +1137,22 @@ bool wave_beats_tile(const fstat_plan* p, const fstat_wu* wu, const Tile& t) {
 // Turns the completed tile into the wave kernel's where the rule (for the
 // default tile) or the tuned class asks for it.
 void pick_wave(const fstat_plan* p, const fstat_wu* wu, Tile& t, bool default_tile_used) {
-  if (!default_tile_used || !wave_beats_tile(p, wu, t)) return;
+  if (!default_tile_used || !p->fits16 || !wave_beats_tile(p, wu, t.pair_seg > 0)) return;
   const int32_t pair_seg = t.pair_seg;
   t = wave_tile();
   t.wave = 1;
   t.pair_seg = pair_seg;             // a work-group of the wave kernel covers both points of a pair
+}
+
+// Whether a call on this unit can launch the wave kernel without waiting for
+// the check: the rule needs nothing from the geometry pass but kGeoFits16,
+// which gates the launch on the device together with the check; no sky pairs
+// (the host makes them from the pass's result) and no toplist (its selection
+// writes outputs whether or not templates were found).
+bool wave_ahead(const fstat_plan* p, const fstat_wu* wu, const fstat_out* o, bool pairs) {
+  auto it = p->tiles.find(class_key(p, wu));
+  return (it == p->tiles.end() || is_wave_tile(it->second)) && !pairs && o->top_k == 0 &&
+         wave_beats_tile(p, wu, false);
 }
 
 // Launch shape of the batched form (a Tile under the plan's batch class):
@@ -1322,6 +1393,9 @@ int batch_interp(fstat_plan* p, const fstat_wu* wus, int n, const fstat_out* out
     rc = ensure_pinned_pair(p, &p->pairs_d, &p->pairs_h, &p->pairs_cap, (size_t)sky_off[n], "sky pairs");
     if (rc) return rc;
   }
+  rc = check_launch(p, fstat::launch_fill_int((int*)p->bstat_d, 0, n * (int)(sizeof(fstat::GeoStatus) / sizeof(int)), st),
+                    "status reset");
+  if (rc) return rc;
   // every work unit is checked before anything is demodulated
   if (groups.size() > 1) {
     for (auto& g : groups) {
@@ -1534,7 +1608,9 @@ int fstat_plan_create(fstat_plan** out, const fstat_desc* d) {
   if (hipMalloc((void**)&p->status_d, sizeof(fstat::GeoStatus)) != hipSuccess ||
       hipHostMalloc((void**)&p->status_h, sizeof(fstat::GeoStatus), hipHostMallocDefault) != hipSuccess ||
       hipEventCreate(&p->ev0) != hipSuccess || hipEventCreate(&p->ev1) != hipSuccess ||
-      hipEventCreateWithFlags(&p->ev_drop, hipEventDisableTiming) != hipSuccess) {
+      hipEventCreateWithFlags(&p->ev_drop, hipEventDisableTiming) != hipSuccess ||
+      hipEventCreate(&p->ev_geo) != hipSuccess ||
+      hipMemset(p->status_d, 0, sizeof(fstat::GeoStatus)) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
     (void)hipGetLastError();
     fstat_plan_destroy(p);
     return FSTAT_E_NOMEM;
@@ -1574,6 +1650,7 @@ void fstat_plan_destroy(fstat_plan* p) {
   if (p->ev0) (void)hipEventDestroy(p->ev0);
   if (p->ev1) (void)hipEventDestroy(p->ev1);
   if (p->ev_drop) (void)hipEventDestroy(p->ev_drop);
+  if (p->ev_geo) (void)hipEventDestroy(p->ev_geo);
   if (p->seg_arena) (void)hipFree(p->seg_arena);
   for (hipEvent_t e : p->seg_ev) (void)hipEventDestroy(e);
   (void)hipGetLastError();
@@ -1586,7 +1663,7 @@ int fstat_compute(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void*
   p->timed = false;
   p->ms_prev = 0.0;
   p->seg_timed = 0;
-  int rc = check_prev_drops(p);
+  int rc = check_prev_drops(p, (hipStream_t)stream);
   if (rc) return rc;
   rc = validate_wu(p, wu, out, -1);
   if (rc) return rc;
@@ -1596,18 +1673,26 @@ int fstat_compute(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void*
   if (rc) return rc;
   rc = ensure_toplist(p, out);
   if (rc) return rc;
-  rc = reset_drops(p, p->status_d, st);
-  if (rc) return rc;
   WuDev v = make_dev(p, wu, out);
-  rc = run_geometry(p, v, st, -1, may_pair(p, wu) ? wu : nullptr);
+  const bool interp = resolved_kernel(p) == fstat::KERNEL_INTERP, pair = may_pair(p, wu);
+  rc = queue_geometry(p, v, p->status_d, st, pair ? wu : nullptr, interp);
   if (rc) return rc;
+  const bool ahead = wave_ahead(p, wu, out, pair);
+  if (ahead) {
+    rc = queue_wave_ahead(p, v, p->status_d, st);
+    if (rc) return rc;
+  }
+  rc = wait_geometry(p, -1);
+  if (rc) p->timed = false;
+  if (rc || (ahead && p->fits16)) return rc;
   bool dflt = false;
   Tile t = pick_tile(p, wu, &dflt);
   rc = prepare_pairs(p, wu, v, t, st, dflt);
   if (rc) return rc;
   pick_wave(p, wu, t, dflt);
-  rc = run_demod(p, v, t, st);
-  if (rc == FSTAT_OK) queue_drop_check(p, p->status_d, p->status_h, 0, st);
+  if (may_drop(resolved_kernel(p), t)) rc = reset_drops(p, p->status_d, st);
+  if (rc == FSTAT_OK) rc = run_demod(p, v, t, st, interp);
+  if (rc == FSTAT_OK) end_call(p, t, resolved_kernel(p), out->top_k > 0, p->status_d, st);
   return rc;
 }
 
@@ -1617,7 +1702,7 @@ int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* ou
   p->timed = false;
   p->ms_prev = 0.0;
   p->seg_timed = 0;
-  int rc = check_prev_drops(p);
+  int rc = check_prev_drops(p, (hipStream_t)stream);
   if (rc) return rc;
   rc = validate_wu(p, wu, out, -1);
   if (rc) return rc;
@@ -1641,8 +1726,6 @@ int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* ou
                    out->top_k, (long long)cap);
   hipStream_t st = (hipStream_t)stream;
   fstat::GeoStatus* status = (fstat::GeoStatus*)(base + fstat::kStaticStatusOff);
-  rc = reset_drops(p, status, st);
-  if (rc) return rc;
   WuDev v = make_dev(p, wu, out);
   char* work = base + fstat::kStaticWorkOff;
   v.geo = (double2*)work;
@@ -1659,14 +1742,23 @@ int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* ou
     v.cand = (uint4*)(base + fstat::kStaticCandOff);
     v.cand_count = (unsigned long long*)(base + fstat::kStaticCountOff);
   }
-  rc = run_geometry_at(p, v, status, st, -1);
+  rc = queue_geometry(p, v, status, st, nullptr, interp);
   if (rc) return rc;
+  const bool ahead = wave_ahead(p, wu, out, false);
+  if (ahead) {
+    rc = queue_wave_ahead(p, v, status, st);
+    if (rc) return rc;
+  }
+  rc = wait_geometry(p, -1);
+  if (rc) p->timed = false;
+  if (rc || (ahead && p->fits16)) return rc;
   bool dflt = false;
   Tile t = pick_tile(p, wu, &dflt);
   t.sblock = 0;                      // one launch over all SFTs: no carried Fa, Fb
   pick_wave(p, wu, t, dflt);
-  rc = run_demod(p, v, t, st);
-  if (rc == FSTAT_OK) queue_drop_check(p, status, p->status_h, 0, st);
+  if (may_drop(resolved_kernel(p), t)) rc = reset_drops(p, status, st);
+  if (rc == FSTAT_OK) rc = run_demod(p, v, t, st, interp);
+  if (rc == FSTAT_OK) end_call(p, t, resolved_kernel(p), out->top_k > 0, status, st);
   return rc;
 }
 
@@ -1676,7 +1768,7 @@ int fstat_batch_compute(fstat_plan* p, const fstat_wu* wus, int32_t n_wu, const 
   p->timed = false;
   p->ms_prev = 0.0;
   p->seg_timed = 0;
-  int rc0 = check_prev_drops(p);
+  int rc0 = check_prev_drops(p, (hipStream_t)stream);
   if (rc0) return rc0;
   if (n_wu < 0 || (n_wu > 0 && (!wus || !outs))) return set_err(p, FSTAT_E_ARG, "bad work-unit list");
   for (int k = 0; k < n_wu; ++k) {
@@ -1688,8 +1780,7 @@ int fstat_batch_compute(fstat_plan* p, const fstat_wu* wus, int32_t n_wu, const 
   if (n_wu == 0) return FSTAT_OK;
   if (resolved_kernel(p) == fstat::KERNEL_INTERP) return batch_interp(p, wus, n_wu, outs, st);
   // direct kernel: one work unit after the other
-  int rc = reset_drops(p, p->status_d, st);
-  if (rc) return rc;
+  int rc = FSTAT_OK;
   for (int k = 0; k < n_wu; ++k) {
     rc = ensure_scratch(p, &wus[k]);
     if (rc) return rc;
@@ -1698,10 +1789,10 @@ int fstat_batch_compute(fstat_plan* p, const fstat_wu* wus, int32_t n_wu, const 
     WuDev v = make_dev(p, &wus[k], &outs[k]);
     rc = run_geometry(p, v, st, k);
     if (rc) return rc;
-    rc = run_demod(p, v, pick_tile(p, &wus[k]), st);
+    rc = run_demod(p, v, pick_tile(p, &wus[k]), st, false);
     if (rc) return rc;
   }
-  queue_drop_check(p, p->status_d, p->status_h, 0, st);
+  end_call(p, Tile{}, fstat::KERNEL_DIRECT, true, p->status_d, st);
   return FSTAT_OK;
 }
 
@@ -1711,7 +1802,7 @@ int fstat_semicoherent(fstat_plan* p, const fstat_wu* segs, int32_t n_seg, const
   p->timed = false;
   p->ms_prev = 0.0;
   p->seg_timed = 0;
-  int rc0 = check_prev_drops(p);
+  int rc0 = check_prev_drops(p, (hipStream_t)stream);
   if (rc0) return rc0;
   if (n_seg < 1 || !segs || !out) return set_err(p, FSTAT_E_ARG, "semi-coherent: need n_seg >= 1 segments and an output");
   if (!out->twoF) return set_err(p, FSTAT_E_ARG, "semi-coherent: the twoF output holds the sum and is required");
@@ -1779,20 +1870,26 @@ int fstat_semicoherent(fstat_plan* p, const fstat_wu* segs, int32_t n_seg, const
     v.geo = (double2*)base;
     v.abcd = (double4*)(base + align256((size_t)n * segs[k].n_sft * sizeof(double2)));
     v.accumulate = k > 0;
-    rc = check_launch(p, fstat::launch_fill_int((int*)(p->bstat_d + k), 0, fstat::kGeoResetInts, st), "status reset");
+    const bool by_kernel = pair && n <= kSkyByKernel;
+    rc = check_launch(p, fstat::launch_geometry(v, p->bstat_d + k, p->bstat_h + k,
+                                                by_kernel ? p->sky_h + 3 * (size_t)n * k : nullptr, st, nullptr),
+                      "geometry kernel");
     if (rc) return rc;
-    rc = check_launch(p, fstat::launch_geometry(v, p->bstat_d + k, st), "geometry kernel");
-    if (rc) return rc;
-    if (pair) {
+    if (pair && !by_kernel) {
       const hipError_t e = hipMemcpyAsync(p->sky_h + 3 * (size_t)n * k, segs[k].sky, (size_t)(3 * n) * sizeof(double),
                                           hipMemcpyDeviceToHost, st);
       if (e != hipSuccess) return hip_err(p, e, "sky vector copy");
     }
     vs[(size_t)k] = v;
   }
-  hipError_t e = hipMemcpyAsync(p->bstat_h, p->bstat_d, (size_t)n_seg * sizeof(fstat::GeoStatus),
-                                hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  // the first segment's coefficients depend on no check and write only scratch
+  hipError_t e = hipEventRecord(p->ev_geo, st);
+  const bool interp = resolved_kernel(p) == fstat::KERNEL_INTERP;
+  if (e == hipSuccess && interp) {
+    rc = run_coef(p, vs[0], st);
+    if (rc) return rc;
+  }
+  if (e == hipSuccess) e = hipEventSynchronize(p->ev_geo);
   if (e != hipSuccess) return hip_err(p, e, "geometry kernel");
   for (int k = 0; k < n_seg; ++k) {
     const int bits = p->bstat_h[k].flags;
@@ -1803,6 +1900,7 @@ int fstat_semicoherent(fstat_plan* p, const fstat_wu* segs, int32_t n_seg, const
     WuDev v = vs[(size_t)k];
     p->max_abs_tau = status_tau(p->bstat_h[k]);       // the slice widths of this segment's tile
     p->max_p = status_p(p->bstat_h[k]);
+    p->fits16 = (p->bstat_h[k].flags & fstat::kGeoFits16) != 0;
     bool dflt = false;
     Tile t = pick_tile(p, &segs[k], &dflt);
     t.pair_seg = 0;
@@ -1812,7 +1910,7 @@ int fstat_semicoherent(fstat_plan* p, const fstat_wu* segs, int32_t n_seg, const
       if (rc) return rc;
     }
     pick_wave(p, &segs[k], t, dflt);
-    rc = run_demod(p, v, t, st, p->seg_ev[2 * (size_t)k], p->seg_ev[2 * (size_t)k + 1]);
+    rc = run_demod(p, v, t, st, interp && k == 0, p->seg_ev[2 * (size_t)k], p->seg_ev[2 * (size_t)k + 1]);
     if (rc) return rc;
   }
   p->seg_timed = n_seg;
@@ -1906,7 +2004,7 @@ int fstat_detector_inputs(fstat_plan* p, const fstat_earth* earth, int32_t n_sit
 int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void* stream, const char* cache_path) {
   if (!p) return FSTAT_E_ARG;
   p->err[0] = 0;
-  int rc = check_prev_drops(p);
+  int rc = check_prev_drops(p, (hipStream_t)stream);
   if (rc) return rc;
   rc = validate_wu(p, wu, out, -1);
   if (rc) return rc;
@@ -1963,7 +2061,7 @@ int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void
               const Tile t{nfd, minw, 0, sb, nt};
               if ((nfd <= 2 * wu->n_fd || nfd == 1) && (nfd == 8 || minw == 3) && valid_tile(p, t)) cands.push_back(t);
             }
-      if (wave_beats_tile(p, wu, complete_tile(p, wu, default_tile(p, wu)))) cands.push_back(wave_tile());
+      if (p->fits16 && wave_beats_tile(p, wu, false)) cands.push_back(wave_tile());
     } else {
       cands = {Tile{1, 16, 0, 0, 0}, Tile{1, 8, 0, 0, 0}, Tile{2, 8, 0, 0, 0}, Tile{2, 4, 0, 0, 0}, Tile{4, 4, 0, 0, 0}};
     }
@@ -1978,7 +2076,7 @@ int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void
       pick_wave(p, wu, t, wave);
       float ms = 0.f;
       for (int rep = 0; rep < 2; ++rep) {
-        rc = run_demod(p, vt, t, st);
+        rc = run_demod(p, vt, t, st, false);
         if (rc) return rc;
         hipError_t e = hipEventSynchronize(p->ev1);
         if (e != hipSuccess) return hip_err(p, e, "autotune");
@@ -1999,7 +2097,7 @@ int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void
   if (!have_b) {
     // the batched launch shape, timed on this unit as a batch of one: the
     // spindown blocking, tiles per chunk of the per-XCD queues, SFTs per launch
-    rc = check_prev_drops(p);
+    rc = check_prev_drops(p, (hipStream_t)stream);
     if (rc) return rc;
     float best = 1e30f;
     Tile best_t = default_batch_tile();
@@ -2016,7 +2114,7 @@ int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void
             if (e != hipSuccess) return hip_err(p, e, "autotune");
             (void)hipEventElapsedTime(&ms, p->ev0, p->ev1);
           }
-          rc = check_prev_drops(p);
+          rc = check_prev_drops(p, (hipStream_t)stream);
           if (rc) return rc;
           if (verbose)
             fprintf(stderr, "[fstat autotune] %s nfd=%d chunk=%d sblock=%d: %.3f ms\n", bkey.c_str(), nfd, chunk, sb,

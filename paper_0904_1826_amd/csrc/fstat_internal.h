@@ -47,6 +47,7 @@ struct WuDev {
   // with an SFT whose windows were not all inside the LDS slice are counted
   // here, and their outputs set to NaN; NULL: not counted
   unsigned long long* dropped;
+  const int* gate;         // wave kernel: NULL, or the geometry pass's gate, 0: write nothing
   int64_t n_sft, n_bins, k_first, n_sky, n_f, n_fd;
   double t_sft, f0, df, fdot0, dfdot, t_ref;
   int32_t dterms;
@@ -120,20 +121,22 @@ struct BatchEntry {
   int64_t sft_begin;    // first SFT in the concatenated SFT list (coef16 exponent pass)
 };
 
-// Geometry pass results read back by the host, and the demodulation's count
-// of tiles that met a slice too narrow for an SFT's windows (reset once per
-// call, not by each geometry pass).
+// Geometry pass results, which the pass copies to the host and clears again
+// (all zero between passes), and the demodulation's count of tiles that met a
+// slice too narrow for an SFT's windows (reset by the calls that may raise it).
 struct GeoStatus {
-  int flags;                  // bit 1: window outside the band; bit 2: AB - C^2 <= 0
-  int pad;
+  int flags;                  // bit 1: window outside the band; bit 2: AB - C^2 <= 0; host copy: kGeoFits16
+  unsigned int arrived;       // blocks of the running pass that have finished
   unsigned long long max_abs_tau_bits;   // max |tau| over (sky, SFT), as FP64 bits
   unsigned long long max_p_bits;         // max Tdot T over (sky, SFT), as FP64 bits
   unsigned long long max_v_bits;         // max |v| over SFTs (units of c), as FP64 bits
   unsigned long long max_r_bits;         // max |r| over SFTs (light-seconds), as FP64 bits
   unsigned long long dropped;            // demodulation: tiles with an SFT outside the slice
+  int gate;                   // the last pass passed its checks and set kGeoFits16
+  int pad;
 };
-// The geometry pass resets the first kGeoResetInts ints (not `dropped`).
-constexpr int kGeoResetInts = 10;
+// A tile of 16 spindowns per thread holds every window in its slice.
+constexpr int kGeoFits16 = 4;
 
 // Static scratch of the no-allocation entry point: one array of this many
 // bytes per device, laid out as the polynomial tables of every Dterms in both
@@ -162,9 +165,17 @@ constexpr int kMaxDterms = 64;
 __host__ __device__ inline int seg_width(int nf, int dterms) { return ((nf + 2 * dterms + 4) + 3) & ~3; }
 
 hipError_t launch_fill_int(int* p, int v, int n, hipStream_t s);
-hipError_t launch_geometry(const WuDev& w, GeoStatus* status, hipStream_t s);
+// Geometry pass with the record `status` (device, zero between passes); the
+// result goes to `host` and the sky vectors to `sky_host` (pinned memory;
+// sky_host may be NULL), complete once `done` (may be NULL) has fired.
+hipError_t launch_geometry(const WuDev& w, GeoStatus* status, GeoStatus* host, double* sky_host, hipStream_t s,
+                           hipEvent_t done);
+// launch_geometry and launch_coef (FP32 coefficients) in one launch.
+hipError_t launch_front(const WuDev& w, GeoStatus* status, GeoStatus* host, double* sky_host, hipStream_t s,
+                        hipEvent_t done);
 hipError_t launch_coef(const WuDev& w, hipStream_t s);
-hipError_t launch_demod(const WuDev& w, const Tile& t, int kernel, hipStream_t s);
+// The demodulation's launches, timed by the events e0 and e1.
+hipError_t launch_demod(const WuDev& w, const Tile& t, int kernel, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 int interp_launches(const WuDev& w, const Tile& t);
 // Tiles of spindowns [fd0, fd1) at nfd per thread and nsky sky points per tile.
 int64_t interp_tiles(const WuDev& w, int nfd, int64_t fd0, int64_t fd1, int nsky);

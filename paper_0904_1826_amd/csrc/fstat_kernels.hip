@@ -11,6 +11,8 @@
 // rounded operation by operation in the order written, which makes k* and
 // kappa identical bit for bit to any other IEEE binary64 evaluation of the
 // same formula.  FP32 fused multiply-adds are written explicitly.
+#include <hip/hip_ext.h>
+
 #include <type_traits>
 
 #include "fstat_internal.h"
@@ -122,88 +124,190 @@ __device__ __forceinline__ void raise_max(unsigned long long* m, double x) {
   if (__hip_atomic_load(m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < b) atomicMax(m, b);
 }
 
-// One block per sky point (grid-stride).  Writes (tau, Tdot) of every SFT and
-// (A, B, C, AB - C^2), and sets status bit 1 if some window of the template
-// grid leaves the band, bit 2 if AB - C^2 <= 0.  k* is monotone in f and in
-// fdot (every rounding step is monotone), so the grid corners bound it.  The
-// status also receives max |tau|, max Tdot T and (from sky point 0's block)
-// max |v| and max |r| over the SFTs, which bound slice widths on the host.
-__global__ __launch_bounds__(256) void geometry_kernel(WuDev w, GeoStatus* status) {
-  __shared__ double red[7][4];
+// Writes (tau, Tdot T) of every SFT and (A, B, C, AB - C^2) of every sky
+// point, and sets status bit 1 if some window of the template grid leaves the
+// band, bit 2 if AB - C^2 <= 0.  k* is monotone in f and in fdot (every
+// rounding step is monotone), so the grid corners bound it.  The status also
+// receives max |tau|, max Tdot T and (from sky point 0) max |v| and max |r|
+// over the SFTs, which bound slice widths on the host.  The last block to
+// finish copies the result to `host` (pinned memory) and clears the record for
+// the next call, so that a call needs neither a launch to reset it nor a copy
+// to read it, and the sky vectors to sky_host, if given.
+//
+// WPS waves share a sky point: 4 (one block per point) where the points are
+// few, 1 where they fill the device anyway, so that fewer blocks arrive at the
+// counter (500 points x 100 SFTs: 24 us with a block each, 17 with a wave each).
+// Either way a sum over SFTs is four partial sums per lane, of the SFTs at
+// 64 c + lane mod 256, reduced in the same order, so A, B, C do not depend on
+// it.
+struct GeoShared {
+  double red[7][4];
+  int bad, last;
+};
+
+template <int WPS>
+__device__ __forceinline__ void geometry_blocks(const WuDev& w, GeoStatus* status, GeoStatus* host, double* sky_host,
+                                                int64_t block, int64_t n_blocks, GeoShared& sh) {
+  constexpr int PPB = 4 / WPS;                     // sky points per block
+  constexpr int NP = 4 / WPS;                      // partial sums per lane
   const double T = w.t_sft;
   const double f_lo = template_f(w, 0), f_hi = template_f(w, w.n_f - 1);
   const double fd_a = template_fd(w, 0), fd_b = template_fd(w, w.n_fd - 1);
   const double band_lo = (double)w.k_first, band_hi = (double)(w.k_first + w.n_bins - 1);
   const int D = w.dterms;
-  for (int64_t s = blockIdx.x; s < w.n_sky; s += gridDim.x) {
-    double A = 0.0, B = 0.0, C = 0.0, tmax = 0.0, pmax = 0.0, vmax = 0.0, rmax = 0.0;
-    int bad = 0;
-    for (int64_t al = threadIdx.x; al < w.n_sft; al += blockDim.x) {
-      double tau, tdot;
-      sft_geometry(w, s, al, tau, tdot);
-      if (s == 0) {
-        const double* r = w.pos + 3 * al;
-        const double* v = w.vel + 3 * al;
-        vmax = fmax(vmax, sqrt((v[0] * v[0] + v[1] * v[1]) + v[2] * v[2]));
-        rmax = fmax(rmax, sqrt((r[0] * r[0] + r[1] * r[1]) + r[2] * r[2]));
+  const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
+  double tmax = 0.0, pmax = 0.0, vmax = 0.0, rmax = 0.0;
+  int bad = 0, singular = 0;
+  for (int64_t s0 = block * PPB; s0 < w.n_sky; s0 += n_blocks * PPB) {
+    const int64_t s = WPS == 4 ? s0 : s0 + wv;
+    double A[NP], B[NP], C[NP];
+#pragma unroll
+    for (int c = 0; c < NP; ++c) A[c] = B[c] = C[c] = 0.0;
+    if (s < w.n_sky) {
+      for (int64_t base = WPS == 4 ? (int64_t)threadIdx.x : (int64_t)ln; base < w.n_sft; base += 256) {
+#pragma unroll
+        for (int c = 0; c < NP; ++c) {
+          const int64_t al = base + 64 * c;
+          if (al >= w.n_sft) break;
+          double tau, tdot;
+          sft_geometry(w, s, al, tau, tdot);
+          if (s == 0) {
+            const double* r = w.pos + 3 * al;
+            const double* v = w.vel + 3 * al;
+            vmax = fmax(vmax, sqrt((v[0] * v[0] + v[1] * v[1]) + v[2] * v[2]));
+            rmax = fmax(rmax, sqrt((r[0] * r[0] + r[1] * r[1]) + r[2] * r[2]));
+          }
+          tmax = fmax(tmax, fabs(tau));
+          const double P = bin_scale(tdot, T);
+          pmax = fmax(pmax, P);
+          w.geo[s * w.n_sft + al] = make_double2(tau, P);
+          const double a = w.a[s * w.n_sft + al], b = w.b[s * w.n_sft + al];
+          A[c] += a * a;
+          B[c] += b * b;
+          C[c] += a * b;
+          const double q_a = bin_offset(fd_a, tau, P), q_b = bin_offset(fd_b, tau, P);
+          const double d1 = bin_position(f_lo, q_a, P), d2 = bin_position(f_lo, q_b, P);
+          const double d3 = bin_position(f_hi, q_a, P), d4 = bin_position(f_hi, q_b, P);
+          const double kmin = floor(d1 < d2 ? (d1 < d3 ? (d1 < d4 ? d1 : d4) : (d3 < d4 ? d3 : d4))
+                                            : (d2 < d3 ? (d2 < d4 ? d2 : d4) : (d3 < d4 ? d3 : d4)));
+          const double kmax = floor(d1 > d2 ? (d1 > d3 ? (d1 > d4 ? d1 : d4) : (d3 > d4 ? d3 : d4))
+                                            : (d2 > d3 ? (d2 > d4 ? d2 : d4) : (d3 > d4 ? d3 : d4)));
+          // NaN fails both comparisons
+          if (!(kmin - (double)(D - 1) >= band_lo && kmax + (double)D <= band_hi)) bad = 1;
+        }
       }
-      tmax = fmax(tmax, fabs(tau));
-      const double P = bin_scale(tdot, T);
-      pmax = fmax(pmax, P);
-      w.geo[s * w.n_sft + al] = make_double2(tau, P);
-      const double a = w.a[s * w.n_sft + al], b = w.b[s * w.n_sft + al];
-      A += a * a;
-      B += b * b;
-      C += a * b;
-      const double q_a = bin_offset(fd_a, tau, P), q_b = bin_offset(fd_b, tau, P);
-      const double d1 = bin_position(f_lo, q_a, P), d2 = bin_position(f_lo, q_b, P);
-      const double d3 = bin_position(f_hi, q_a, P), d4 = bin_position(f_hi, q_b, P);
-      const double kmin = floor(d1 < d2 ? (d1 < d3 ? (d1 < d4 ? d1 : d4) : (d3 < d4 ? d3 : d4))
-                                        : (d2 < d3 ? (d2 < d4 ? d2 : d4) : (d3 < d4 ? d3 : d4)));
-      const double kmax = floor(d1 > d2 ? (d1 > d3 ? (d1 > d4 ? d1 : d4) : (d3 > d4 ? d3 : d4))
-                                        : (d2 > d3 ? (d2 > d4 ? d2 : d4) : (d3 > d4 ? d3 : d4)));
-      // NaN fails both comparisons
-      if (!(kmin - (double)(D - 1) >= band_lo && kmax + (double)D <= band_hi)) bad = 1;
-    }
-    A = warp_sum(A);
-    B = warp_sum(B);
-    C = warp_sum(C);
-    for (int o = 32; o > 0; o >>= 1) tmax = fmax(tmax, __shfl_xor(tmax, o, 64));
-    for (int o = 32; o > 0; o >>= 1) pmax = fmax(pmax, __shfl_xor(pmax, o, 64));
-    for (int o = 32; o > 0; o >>= 1) vmax = fmax(vmax, __shfl_xor(vmax, o, 64));
-    for (int o = 32; o > 0; o >>= 1) rmax = fmax(rmax, __shfl_xor(rmax, o, 64));
-    const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-    if (ln == 0) {
-      red[0][wv] = A; red[1][wv] = B; red[2][wv] = C; red[3][wv] = tmax; red[4][wv] = pmax;
-      red[5][wv] = vmax; red[6][wv] = rmax;
-    }
-    const int any_bad = __syncthreads_or(bad);
-    if (threadIdx.x == 0) {
-      A = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-      B = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
-      C = (red[2][0] + red[2][1]) + (red[2][2] + red[2][3]);
-      const double Dd = A * B - C * C;
-      w.abcd[s] = make_double4(A, B, C, Dd);
-      int flags = any_bad ? 1 : 0;
-      if (!(Dd > 0.0)) flags |= 2;
-      if (flags) atomicOr(&status->flags, flags);
-      // the maxima are non-negative, so their bits order as the values; a
-      // block whose value does not exceed the one already stored skips the
-      // atomic (the stored value only grows), which keeps thousands of blocks
-      // from queueing on one address
-      const double tm = fmax(fmax(red[3][0], red[3][1]), fmax(red[3][2], red[3][3]));
-      raise_max(&status->max_abs_tau_bits, tm);
-      const double pm = fmax(fmax(red[4][0], red[4][1]), fmax(red[4][2], red[4][3]));
-      raise_max(&status->max_p_bits, pm);
-      if (s == 0) {
-        const double vm = fmax(fmax(red[5][0], red[5][1]), fmax(red[5][2], red[5][3]));
-        const double rm = fmax(fmax(red[6][0], red[6][1]), fmax(red[6][2], red[6][3]));
-        raise_max(&status->max_v_bits, vm);
-        raise_max(&status->max_r_bits, rm);
+#pragma unroll
+      for (int c = 0; c < NP; ++c) {
+        A[c] = warp_sum(A[c]);
+        B[c] = warp_sum(B[c]);
+        C[c] = warp_sum(C[c]);
       }
     }
-    __syncthreads();
+    double a4[4], b4[4], c4[4];
+    if constexpr (WPS == 4) {
+      __syncthreads();                             // sh.red of the previous point is consumed
+      if (ln == 0) {
+        sh.red[0][wv] = A[0];
+        sh.red[1][wv] = B[0];
+        sh.red[2][wv] = C[0];
+      }
+      __syncthreads();
+      if (threadIdx.x != 0) continue;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        a4[c] = sh.red[0][c];
+        b4[c] = sh.red[1][c];
+        c4[c] = sh.red[2][c];
+      }
+    } else {
+      if (ln != 0 || s >= w.n_sky) continue;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        a4[c] = A[c];
+        b4[c] = B[c];
+        c4[c] = C[c];
+      }
+    }
+    const double a = (a4[0] + a4[1]) + (a4[2] + a4[3]), b = (b4[0] + b4[1]) + (b4[2] + b4[3]);
+    const double c = (c4[0] + c4[1]) + (c4[2] + c4[3]);
+    const double dd = a * b - c * c;
+    w.abcd[s] = make_double4(a, b, c, dd);
+    if (!(dd > 0.0)) singular = 1;
   }
+  for (int o = 32; o > 0; o >>= 1) {
+    tmax = fmax(tmax, __shfl_xor(tmax, o, 64));
+    pmax = fmax(pmax, __shfl_xor(pmax, o, 64));
+    vmax = fmax(vmax, __shfl_xor(vmax, o, 64));
+    rmax = fmax(rmax, __shfl_xor(rmax, o, 64));
+  }
+  if (ln == 0) {
+    sh.red[3][wv] = tmax;
+    sh.red[4][wv] = pmax;
+    sh.red[5][wv] = vmax;
+    sh.red[6][wv] = rmax;
+  }
+  const int any_bad = __syncthreads_or(bad), any_singular = __syncthreads_or(singular);
+  if (threadIdx.x == 0) {
+    const int flags = (any_bad ? 1 : 0) | (any_singular ? 2 : 0);
+    if (flags) atomicOr(&status->flags, flags);
+    // the maxima are non-negative, so their bits order as the values; a block
+    // whose value does not exceed the one already stored skips the atomic (the
+    // stored value only grows), which keeps hundreds of blocks from queueing
+    // on one address
+    double m[4];
+    for (int x = 0; x < 4; ++x)
+      m[x] = fmax(fmax(sh.red[3 + x][0], sh.red[3 + x][1]), fmax(sh.red[3 + x][2], sh.red[3 + x][3]));
+    raise_max(&status->max_abs_tau_bits, m[0]);
+    raise_max(&status->max_p_bits, m[1]);
+    if (block == 0) {                              // sky point 0's block
+      raise_max(&status->max_v_bits, m[2]);
+      raise_max(&status->max_r_bits, m[3]);
+    }
+    // The status is only touched by device-scope atomics, so a block need only
+    // have completed its own before it arrives (a fence here would write its
+    // XCD's L2 back once per block).
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    sh.last = atomicAdd(&status->arrived, 1u) == (unsigned)n_blocks - 1u;
+  }
+  __syncthreads();
+  if (!sh.last) return;
+  if (sky_host)
+    for (int64_t e = threadIdx.x; e < 3 * w.n_sky; e += blockDim.x) sky_host[e] = w.sky[e];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  int flags = atomicExch(&status->flags, 0);
+  const unsigned long long tb = atomicExch(&status->max_abs_tau_bits, 0ull);
+  const unsigned long long pb = atomicExch(&status->max_p_bits, 0ull);
+  // whether a block of 16 spindowns fits the slice (as the host sizes slices)
+  const double spread = (255.0 * w.df + fabs(w.dfdot) * 15.0 * __longlong_as_double((long long)tb)) *
+                        __longlong_as_double((long long)pb);
+  if (spread <= 255.0 + (double)((w.coef16 ? kSegMax16 : kSegMax) - 262)) flags |= kGeoFits16;
+  status->gate = flags == kGeoFits16 ? 1 : 0;
+  host->max_abs_tau_bits = tb;
+  host->max_p_bits = pb;
+  host->max_v_bits = atomicExch(&status->max_v_bits, 0ull);
+  host->max_r_bits = atomicExch(&status->max_r_bits, 0ull);
+  host->flags = flags;
+  atomicExch(&status->arrived, 0u);
+  __threadfence_system();
+}
+
+// Sky points from which a wave takes a whole point, and the blocks of the pass.
+constexpr int64_t kGeoWavePoints = 128;
+static int64_t geometry_grid(const WuDev& w) {
+  if (w.n_sky < kGeoWavePoints) return w.n_sky;
+  const int64_t b = (w.n_sky + 3) / 4;
+  return b < 512 ? b : 512;
+}
+
+__global__ __launch_bounds__(256) void geometry_kernel(WuDev w, GeoStatus* status, GeoStatus* host,
+                                                       double* sky_host) {
+  __shared__ GeoShared sh;
+  if (w.n_sky < kGeoWavePoints)
+    geometry_blocks<4>(w, status, host, sky_host, blockIdx.x, gridDim.x, sh);
+  else
+    geometry_blocks<1>(w, status, host, sky_host, blockIdx.x, gridDim.x, sh);
 }
 
 // ------------------------------------------------------ Dirichlet window
@@ -502,6 +606,20 @@ __global__ __launch_bounds__(256) void coef_kernel(WuDev w) {
   __shared__ float2 xs[256 + 2 * kMaxDterms];
   __shared__ double tab[2 * kMaxDterms * kCoef];
   coef_block<C16>(w, blockIdx.x, xs, tab);
+}
+
+// Geometry and coefficients of a small unit in one launch: the first n_geo
+// blocks are the geometry pass's, the rest the coefficient pass's, which does
+// not depend on it.
+__global__ __launch_bounds__(256) void front_kernel(WuDev w, GeoStatus* status, GeoStatus* host, double* sky_host,
+                                                    int n_geo) {
+  __shared__ GeoShared sh;
+  __shared__ float2 xs[256 + 2 * kMaxDterms];
+  __shared__ double tab[2 * kMaxDterms * kCoef];
+  if ((int)blockIdx.x < n_geo)
+    geometry_blocks<4>(w, status, host, sky_host, blockIdx.x, n_geo, sh);
+  else
+    coef_block<false>(w, (int64_t)blockIdx.x - n_geo, xs, tab);
 }
 
 // The coefficient pass of many work units in one launch; block b belongs to
@@ -1263,6 +1381,7 @@ __global__ __launch_bounds__(kThreads, 3) void demod_wave_kernel(WuDev w) {
   // alternate between two register sets
   static_assert(64 % (2 * kAhead) == 0, "a block holds whole pairs of groups");
   fetch(0);
+  if (w.gate && !*w.gate) return;                  // launched ahead of the check, which failed
   publish(0);
   if (n > 64) fetch(64);
   Group ga, gb;
@@ -1419,13 +1538,25 @@ hipError_t launch_fill_int(int* p, int v, int n, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_geometry(const WuDev& w, GeoStatus* status, hipStream_t st) {
-  const int64_t blocks = w.n_sky < 65536 ? w.n_sky : 65536;
-  hipLaunchKernelGGL(geometry_kernel, dim3((unsigned)blocks), dim3(256), 0, st, w, status);
+hipError_t launch_geometry(const WuDev& w, GeoStatus* status, GeoStatus* host, double* sky_host, hipStream_t st,
+                           hipEvent_t done) {
+  const int64_t blocks = geometry_grid(w);
+  // the event rides on the kernel's own completion signal: no packet of its own
+  hipExtLaunchKernelGGL(geometry_kernel, dim3((unsigned)blocks), dim3(256), 0, st, nullptr, done, 0, w, status, host,
+                        sky_host);
   return hipGetLastError();
 }
 
 int64_t coef_blocks(const WuDev& w) { return ((w.n_bins + 255) / 256) * w.n_sft; }
+
+hipError_t launch_front(const WuDev& w, GeoStatus* status, GeoStatus* host, double* sky_host, hipStream_t st,
+                        hipEvent_t done) {
+  const int64_t blocks = w.n_sky + coef_blocks(w);
+  if (w.coef16 || w.n_sky > 256 || blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+  hipExtLaunchKernelGGL(front_kernel, dim3((unsigned)blocks), dim3(256), 0, st, nullptr, done, 0, w, status, host,
+                        sky_host, (int)w.n_sky);
+  return hipGetLastError();
+}
 
 hipError_t launch_coef(const WuDev& w, hipStream_t st) {
   const int64_t blocks = coef_blocks(w);
@@ -1695,7 +1826,7 @@ static hipError_t launch_interp(const WuDev& w, const Tile& t, hipStream_t st) {
 }
 
 // One wave per (sky point, spindown, 64 frequencies), t.wave set.
-static hipError_t launch_wave(const WuDev& w, hipStream_t st) {
+static hipError_t launch_wave(const WuDev& w, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   const bool pairs = w.n_pairs > 0;
   const int per = wave_spindowns(pairs, w.n_fd);
   const int64_t nf = pairs ? 64 : 256 / per;       // frequencies per work-group
@@ -1703,9 +1834,9 @@ static hipError_t launch_wave(const WuDev& w, hipStream_t st) {
       ((w.n_f + nf - 1) / nf) * ((w.n_fd + per - 1) / per) * (pairs ? w.n_pairs : w.n_sky);
   if (blocks <= 0 || blocks > 0x7fffffffLL || (w.n_pairs > 0 && !w.sky_pairs)) return hipErrorInvalidConfiguration;
   if (w.coef16)
-    hipLaunchKernelGGL(demod_wave_kernel<true>, dim3((unsigned)blocks), dim3(kThreads), 0, st, w);
+    hipExtLaunchKernelGGL(demod_wave_kernel<true>, dim3((unsigned)blocks), dim3(kThreads), 0, st, e0, e1, 0, w);
   else
-    hipLaunchKernelGGL(demod_wave_kernel<false>, dim3((unsigned)blocks), dim3(kThreads), 0, st, w);
+    hipExtLaunchKernelGGL(demod_wave_kernel<false>, dim3((unsigned)blocks), dim3(kThreads), 0, st, e0, e1, 0, w);
   return hipGetLastError();
 }
 
@@ -1768,13 +1899,22 @@ static hipError_t launch_direct_d(const WuDev& w, const Tile& t, hipStream_t st)
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_demod(const WuDev& w, const Tile& t, int kernel, hipStream_t st) {
-  if (kernel == KERNEL_INTERP) return t.wave ? launch_wave(w, st) : launch_interp(w, t, st);
+static hipError_t launch_tiles(const WuDev& w, const Tile& t, int kernel, hipStream_t st) {
+  if (kernel == KERNEL_INTERP) return launch_interp(w, t, st);
   switch (w.dterms) {
     case 8: return launch_direct_d<8>(w, t, st);
     case 16: return launch_direct_d<16>(w, t, st);
     default: return launch_direct_d<0>(w, t, st);
   }
+}
+
+hipError_t launch_demod(const WuDev& w, const Tile& t, int kernel, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  // one launch of a small unit: the events take the kernel's own time stamps
+  if (kernel == KERNEL_INTERP && t.wave) return launch_wave(w, st, e0, e1);
+  (void)hipEventRecord(e0, st);
+  const hipError_t e = launch_tiles(w, t, kernel, st);
+  (void)hipEventRecord(e1, st);
+  return e;
 }
 
 hipError_t launch_bins(const WuDev& w, int64_t n, const int32_t* i_sky, const int32_t* i_fd, const int32_t* i_f,
