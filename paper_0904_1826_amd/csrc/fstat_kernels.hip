@@ -1436,15 +1436,108 @@ struct BatchSeg {
   __device__ const WuDev& unit(int q) const { return ents[q].w; }
 };
 
-// Slots past a segment's count become sentinels that rank last.
+__device__ __forceinline__ int64_t cand_held(const WuDev& w, int64_t cap) {
+  const unsigned long long cnt = *w.cand_count;
+  return cnt < (unsigned long long)cap ? (int64_t)cnt : cap;
+}
+
+// One toplist entry: the candidate decoded to (2F, sky, fdot, f).
+__device__ __forceinline__ int4 top_entry(const WuDev& w, uint4 c) {
+  const int64_t o = (int64_t)(((uint64_t)c.w << 32) | c.z);
+  const int64_t per_sky = w.n_fd * w.n_f;
+  const int64_t s = o / per_sky, r = o - s * per_sky;
+  return make_int4((int)c.x, (int)s, (int)(r / w.n_f), (int)(r % w.n_f));
+}
+
+// Selection in two launches.  The first sorts the candidates a segment holds
+// (not its capacity) in chunks of kSortChunk in LDS, best first; a segment of
+// one chunk, the usual case, is then complete and its toplist is written.
+// The second ranks the entries of larger segments: an entry's rank is the sum
+// over the chunks of the better entries there (a binary search each), given up
+// once it reaches top_k.  A bitonic sort over the whole capacity takes 136
+// launches at 65536 entries, 0.54 ms whatever the count.
+constexpr int kSortChunk = 4096;
+constexpr int kSortThreads = 1024;
+
+template <class Seg>
+__global__ __launch_bounds__(kSortThreads) void cand_chunk_kernel(Seg seg, uint4* cand, int64_t cap) {
+  const int q = blockIdx.y;
+  const WuDev& w = seg.unit(q);
+  if (!w.cand || w.top_k <= 0) return;
+  const int64_t n = cand_held(w, cap), c0 = (int64_t)blockIdx.x * kSortChunk;
+  if (blockIdx.x > 0 && c0 >= n) return;
+  __shared__ uint4 x[kSortChunk];
+  uint4* src = cand + (int64_t)q * cap + c0;
+  const int m = (int)(n - c0 < kSortChunk ? n - c0 : kSortChunk);
+  int len = 1;
+  while (len < m) len <<= 1;
+  for (int i = threadIdx.x; i < len; i += kSortThreads)   // sentinels past the count rank last
+    x[i] = i < m ? src[i] : make_uint4(__float_as_uint(-__builtin_huge_valf()), 0u, ~0u, ~0u);
+  for (int k = 2; k <= len; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      __syncthreads();
+      for (int t = threadIdx.x; t < len / 2; t += kSortThreads) {
+        const int i = 2 * t - (t & (j - 1)), p = i | j;
+        const uint4 a = x[i], b = x[p];
+        if ((i & k) == 0 ? cand_better(b, a) : cand_better(a, b)) {
+          x[i] = b;
+          x[p] = a;
+        }
+      }
+    }
+  __syncthreads();
+  if (n > kSortChunk) {
+    for (int i = threadIdx.x; i < m; i += kSortThreads) src[i] = x[i];
+    return;
+  }
+  if (threadIdx.x == 0) *w.n_above = *w.cand_count;
+  for (int t = threadIdx.x; t < w.top_k; t += kSortThreads)
+    w.top[t] = t < n ? top_entry(w, x[t]) : make_int4(0, -1, -1, -1);
+}
+
+template <class Seg>
+__global__ __launch_bounds__(256) void cand_rank_kernel(Seg seg, const uint4* cand, int64_t cap) {
+  const int q = blockIdx.y;
+  const WuDev& w = seg.unit(q);
+  if (!w.cand || w.top_k <= 0) return;
+  const int64_t n = cand_held(w, cap);
+  if (n <= kSortChunk) return;                     // complete
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i == 0) *w.n_above = *w.cand_count;
+  if (i >= n) {
+    if (i < w.top_k) w.top[i] = make_int4(0, -1, -1, -1);
+    return;
+  }
+  const uint4* base = cand + (int64_t)q * cap;
+  const int64_t own = i / kSortChunk;
+  int64_t rank = i - own * kSortChunk;
+  const uint4 me = base[i];
+  for (int64_t c = 0; c * kSortChunk < n && rank < w.top_k; ++c) {
+    if (c == own) continue;
+    int64_t lo = c * kSortChunk, hi = lo + kSortChunk < n ? lo + kSortChunk : n;
+    const int64_t first = lo;
+    while (lo < hi) {                              // the entries of chunk c that are better
+      const int64_t mid = (lo + hi) >> 1;
+      if (cand_better(base[mid], me)) lo = mid + 1;
+      else hi = mid;
+    }
+    rank += lo - first;
+  }
+  if (rank < w.top_k) w.top[rank] = top_entry(w, me);
+}
+
+// Toplists of more than kRankTopK entries, whose ranks would not be given up
+// early: a bitonic sort of every segment, then its first top_k entries.  Slots
+// past a segment's count become sentinels that rank last.
+constexpr int kRankTopK = 65536;
+
 template <class Seg>
 __global__ __launch_bounds__(256) void cand_pad_kernel(Seg seg, uint4* cand, int64_t cap, int64_t total) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= total) return;
   const int q = (int)(i / cap);
   const WuDev& w = seg.unit(q);
-  const unsigned long long cnt = w.cand_count ? *w.cand_count : 0ull;
-  const int64_t n = cnt < (unsigned long long)cap ? (int64_t)cnt : cap;
+  const int64_t n = w.cand_count ? cand_held(w, cap) : 0;
   if ((i & (cap - 1)) >= n) cand[i] = make_uint4(__float_as_uint(-__builtin_huge_valf()), 0u, ~0u, ~0u);
 }
 
@@ -1472,19 +1565,9 @@ __global__ __launch_bounds__(256) void top_write_kernel(Seg seg, const uint4* ca
   const WuDev& w = seg.unit(q);
   if (!w.cand || w.top_k <= 0) return;
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const unsigned long long cnt = *w.cand_count;
-  if (t == 0) *w.n_above = cnt;
+  if (t == 0) *w.n_above = *w.cand_count;
   if (t >= w.top_k) return;
-  const int64_t n = cnt < (unsigned long long)cap ? (int64_t)cnt : cap;
-  if (t >= n) {
-    w.top[t] = make_int4(0, -1, -1, -1);
-    return;
-  }
-  const uint4 c = cand[(int64_t)q * cap + t];
-  const int64_t o = (int64_t)(((uint64_t)c.w << 32) | c.z);
-  const int64_t per_sky = w.n_fd * w.n_f;
-  const int64_t s = o / per_sky, r = o - s * per_sky;
-  w.top[t] = make_int4((int)c.x, (int)s, (int)(r / w.n_f), (int)(r % w.n_f));
+  w.top[t] = t < cand_held(w, cap) ? top_entry(w, cand[(int64_t)q * cap + t]) : make_int4(0, -1, -1, -1);
 }
 
 // ------------------------------------------------------------ bin probe
@@ -1845,6 +1928,16 @@ static hipError_t top_select(const Seg& seg, int n_seg, uint4* cand, int64_t cap
   const int64_t total = (int64_t)n_seg * cap;
   if (n_seg <= 0 || cap <= 0 || (cap & (cap - 1)) != 0 || total / 256 + 1 > 0x7fffffffLL)
     return hipErrorInvalidConfiguration;
+  if (max_top_k <= kRankTopK) {
+    if (max_top_k <= 0) return hipSuccess;
+    const dim3 chunks((unsigned)((cap + kSortChunk - 1) / kSortChunk), (unsigned)n_seg);
+    hipLaunchKernelGGL(cand_chunk_kernel<Seg>, chunks, dim3(kSortThreads), 0, st, seg, cand, cap);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || cap <= kSortChunk) return e;
+    const dim3 entries((unsigned)((cap + 255) / 256), (unsigned)n_seg);
+    hipLaunchKernelGGL(cand_rank_kernel<Seg>, entries, dim3(256), 0, st, seg, (const uint4*)cand, cap);
+    return hipGetLastError();
+  }
   const dim3 grid((unsigned)((total + 255) / 256)), block(256);
   hipLaunchKernelGGL(cand_pad_kernel<Seg>, grid, block, 0, st, seg, cand, cap, total);
   hipError_t e = hipGetLastError();
@@ -1854,7 +1947,6 @@ static hipError_t top_select(const Seg& seg, int n_seg, uint4* cand, int64_t cap
       e = hipGetLastError();
     }
   if (e != hipSuccess) return e;
-  if (max_top_k <= 0) return hipSuccess;
   hipLaunchKernelGGL(top_write_kernel<Seg>, dim3((unsigned)((max_top_k + 255) / 256), (unsigned)n_seg), block, 0, st,
                      seg, (const uint4*)cand, cap);
   return hipGetLastError();
