@@ -238,10 +238,12 @@ int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* ou
  * with SFTs left; inside a launch the tiles are dealt to one queue per XCD in
  * chunks of consecutive tiles, so that tiles sharing coefficients are served
  * by one L2.  All
- * work units are validated and band-checked before anything is launched; on
+ * work units are validated and band-checked before any output is written (the
+ * coefficient passes, which write only scratch, run meanwhile); on
  * failure the index of the first failing work unit is in fstat_last_error.
- * The launch sequence is captured once in a hipGraph per signature (table
- * address and shape, SFT blocks, kernel variants, toplist buffers) and
+ * The demodulation's launch sequence is captured once in a hipGraph per
+ * signature (table address and shape, SFT blocks, kernel variants, toplist
+ * buffers), the tables of different block sizes in two parallel chains, and
  * replayed; the work-unit table lives in device memory, so a replay may
  * change every pointer and size of the units.  Plan scratch per unit:
  * geometry (16 B per sky point and SFT), coefficients (64 B per SFT and bin,

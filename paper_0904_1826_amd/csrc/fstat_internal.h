@@ -183,7 +183,7 @@ int64_t coef_blocks(const WuDev& w);
 hipError_t launch_coef_batch(const BatchEntry* ents_dev, int n_ent, int64_t total_blocks, bool c16, hipStream_t s);
 // SFTs [al0, al1) of the first n_ent entries (each clipped to its unit's
 // SFT count; every one of them must have more than al0 SFTs).
-// Tiles are dealt to kXcds queues (counters[0, kXcds)) in chunks of `chunk`.
+// Tiles are dealt to kXcds queues (counters[0, kXcds), cleared by the caller) in chunks of `chunk`.
 // The batched kernel exists for split_nfd(i) spindowns per thread, i <
 // kSplitSizes (with FP16 coefficients for 8 and 4 only), with one sky point
 // per tile, and for 4 to 8 (FP32 coefficients) with tiles of two

@@ -1723,9 +1723,6 @@ hipError_t launch_interp_batch(const BatchEntry* ents_dev, int n_ent, int64_t to
   if (al0 < 0 || al1 <= al0 || chunk < 1) return hipErrorInvalidValue;
   if (c16 ? (nfd != 8 && nfd != 4) : ((nfd < 4 || nfd > 8) && nfd != 16)) return hipErrorInvalidValue;
   if (nsky != 1 && (nsky != 2 || c16 || nfd > 8)) return hipErrorInvalidValue;
-  // kernel, not memset: safe under capture
-  hipError_t e = launch_fill_int((int*)counters, 0, 2 * kXcds, st);
-  if (e != hipSuccess) return e;
   const dim3 g((unsigned)grid), b(kThreads);
 #define FSTAT_BATCH_LAUNCH(N, C, SF) \
   hipLaunchKernelGGL((demod_interp_batch_kernel<N, C, SF>), g, b, 0, st, ents_dev, n_ent, total_tiles, counters, \
