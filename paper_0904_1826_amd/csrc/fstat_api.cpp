@@ -56,9 +56,6 @@ struct fstat_plan {
   size_t bcand_bytes = 0;
   void* bcount = nullptr;
   size_t bcount_bytes = 0;
-  // detector inputs: per-SFT detector tensors
-  void* dten = nullptr;
-  size_t dten_bytes = 0;
   // timing
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   hipStream_t ev_stream = nullptr;
@@ -1711,7 +1708,6 @@ void fstat_plan_destroy(fstat_plan* p) {
   if (p->cand_count) (void)hipFree(p->cand_count);
   if (p->bcand) (void)hipFree(p->bcand);
   if (p->bcount) (void)hipFree(p->bcount);
-  if (p->dten) (void)hipFree(p->dten);
   for (auto& kv : p->ctab) (void)hipFree(kv.second);
   if (p->status_d) (void)hipFree(p->status_d);
   if (p->status_h) (void)hipHostFree(p->status_h);
@@ -2053,7 +2049,8 @@ int fstat_detector_inputs(fstat_plan* p, const fstat_earth* earth, int32_t n_sit
   m.orbit_radius = earth->orbit_radius;
   m.orbit_rate = earth->orbit_rate;
   m.orbit_phase = earth->orbit_phase;
-  m.obliquity = earth->obliquity;
+  m.se = sin(earth->obliquity);
+  m.ce = cos(earth->obliquity);
   m.earth_radius = earth->earth_radius;
   m.sidereal_rate = earth->sidereal_rate;
   m.sidereal_phase = earth->sidereal_phase;
@@ -2062,15 +2059,14 @@ int fstat_detector_inputs(fstat_plan* p, const fstat_earth* earth, int32_t n_sit
     const fstat_site& s = sites[k];
     if (!std::isfinite(s.lat) || !std::isfinite(s.lon) || !std::isfinite(s.az_x) || !std::isfinite(s.az_y))
       return set_err(p, FSTAT_E_ARG, "non-finite site %d", k);
-    m.sites[k] = fstat::SiteModel{s.lat, s.lon, s.az_x, s.az_y};
+    m.sites[k] = fstat::SiteModel{s.lon,       sin(s.lat),  cos(s.lat), sin(s.az_x),
+                                  cos(s.az_x), sin(s.az_y), cos(s.az_y)};
   }
   if (hipSetDevice(p->device) != hipSuccess) return set_err(p, FSTAT_E_DEVICE, "hipSetDevice failed");
-  int rc = dev_alloc(p, &p->dten, &p->dten_bytes, (size_t)n_sft * 6 * sizeof(double), "detector tensors");
-  if (rc) return rc;
   return check_launch(p,
-                      fstat::launch_detector_inputs(m, n_sft, t_mid, site_of_sft, n_sky, sky, pos, vel,
-                                                    (double*)p->dten, a, b, (hipStream_t)stream),
-                      "detector input kernels");
+                      fstat::launch_detector_inputs(m, n_sft, t_mid, site_of_sft, n_sky, sky, pos, vel, a, b,
+                                                    (hipStream_t)stream),
+                      "detector input kernel");
 }
 
 int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void* stream, const char* cache_path) {

@@ -550,14 +550,17 @@ __device__ __forceinline__ float pack_h2(double re, double im) {
   return __builtin_bit_cast(float, h);
 }
 
+//
+// The table is read through scalar loads (every lane of a wave wants the same
+// eight values; from LDS they cost more cycles than the sixteen FMAs they
+// feed), so the pass is bound by its FP64 FMAs.
 template <bool C16>
-__device__ __forceinline__ void coef_block(const WuDev& w, int64_t block, float2* xs, double* tab) {
+__device__ __forceinline__ void coef_block(const WuDev& w, int64_t block, float2* xs) {
   const int D = w.dterms;
   const int64_t n_cc = (w.n_bins + 255) / 256;
   const int64_t al = block / n_cc;
   const int64_t c0 = (block % n_cc) * 256;
   const int tid = threadIdx.x;
-  for (int e = tid; e < 2 * D * kCoef; e += 256) tab[e] = w.ctab[e];
   for (int e = tid; e < 256 + 2 * D; e += 256) {
     const int64_t n = c0 - D + e;
     float2 v = make_float2(0.f, 0.f);
@@ -574,9 +577,11 @@ __device__ __forceinline__ void coef_block(const WuDev& w, int64_t block, float2
 #pragma unroll
   for (int p = 0; p < kCoef; ++p) cr[p] = ci[p] = 0.0;
   if (c >= D - 1 && c <= w.n_bins - 1 - D) {
+    typedef const __attribute__((address_space(4))) double* TablePtr;   // constant: scalar loads
+    const TablePtr tab = (TablePtr)(uintptr_t)w.ctab;
     for (int m = -D; m < D; ++m) {
       const float2 x = xs[tid + D - m];                         // bin k - m
-      const double* t = tab + (m + D) * kCoef;
+      const TablePtr t = tab + (m + D) * kCoef;
 #pragma unroll
       for (int p = 0; p < kCoef; ++p) {
         cr[p] = __builtin_fma((double)x.x, t[p], cr[p]);
@@ -604,8 +609,7 @@ __device__ __forceinline__ void coef_block(const WuDev& w, int64_t block, float2
 template <bool C16>
 __global__ __launch_bounds__(256) void coef_kernel(WuDev w) {
   __shared__ float2 xs[256 + 2 * kMaxDterms];
-  __shared__ double tab[2 * kMaxDterms * kCoef];
-  coef_block<C16>(w, blockIdx.x, xs, tab);
+  coef_block<C16>(w, blockIdx.x, xs);
 }
 
 // Geometry and coefficients of a small unit in one launch: the first n_geo
@@ -615,11 +619,10 @@ __global__ __launch_bounds__(256) void front_kernel(WuDev w, GeoStatus* status, 
                                                     int n_geo) {
   __shared__ GeoShared sh;
   __shared__ float2 xs[256 + 2 * kMaxDterms];
-  __shared__ double tab[2 * kMaxDterms * kCoef];
   if ((int)blockIdx.x < n_geo)
     geometry_blocks<4>(w, status, host, sky_host, blockIdx.x, n_geo, sh);
   else
-    coef_block<false>(w, (int64_t)blockIdx.x - n_geo, xs, tab);
+    coef_block<false>(w, (int64_t)blockIdx.x - n_geo, xs);
 }
 
 // The coefficient pass of many work units in one launch; block b belongs to
@@ -627,7 +630,6 @@ __global__ __launch_bounds__(256) void front_kernel(WuDev w, GeoStatus* status, 
 template <bool C16>
 __global__ __launch_bounds__(256) void coef_batch_kernel(const BatchEntry* __restrict__ ents, int n_ent) {
   __shared__ float2 xs[256 + 2 * kMaxDterms];
-  __shared__ double tab[2 * kMaxDterms * kCoef];
   const int64_t b = blockIdx.x;
   int lo = 0, hi = n_ent - 1;
   while (lo < hi) {
@@ -635,7 +637,7 @@ __global__ __launch_bounds__(256) void coef_batch_kernel(const BatchEntry* __res
     if (ents[mid].coef_begin <= b) lo = mid; else hi = mid - 1;
   }
   const WuDev w = ents[lo].w;
-  coef_block<C16>(w, b - ents[lo].coef_begin, xs, tab);
+  coef_block<C16>(w, b - ents[lo].coef_begin, xs);
 }
 
 // Per-SFT exponent of the FP16 coefficient form: e = (binary exponent of
