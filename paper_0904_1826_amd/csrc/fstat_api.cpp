@@ -1126,32 +1126,32 @@ int prepare_pairs(fstat_plan* p, const fstat_wu* wu, WuDev& v, Tile& t, hipStrea
 // Whether demod_wave_kernel is expected to beat the interp tile `t` (already
 // completed for the unit) on this unit.  Both are modelled as time per SFT,
 // measured on 1 to 900 sky points x 1 to 40 spindowns x 1800 frequencies:
-// - the wave kernel takes 0.19 us + 2.27e-6 us per template (1.27e-6 with FP16
-//   coefficients, whose loads are half as wide): 0.30 us at 5e4 templates,
-//   1.11 at 4e5, 3.7 at 1.6e6 (4.3e11 pairs/s, the rate of its 64-byte loads);
+// - the wave kernel takes 0.11 us + 2.2e-6 us per template (1.25e-6 with FP16
+//   coefficients, whose loads are half as wide): 0.24 us at 5e4 templates,
+//   1.04 at 4e5, 1.98 at 8.6e5 (4.5e11 pairs/s, the rate of its 64-byte loads);
 // - the tile kernels, however few their tiles, take the latency of a staged
-//   slice, a barrier and a thread's spindowns per SFT and launch: 1.04 us with
-//   4 per thread, 1.21 with 5, 1.29 with 6 or 7, 1.46 with 8, 2.17 with 16
-//   (FP16 coefficients 1.28 with 8), summed over the ranges of a split, whose
-//   launches follow each other; they come down to 1.05e-6 us per template.
-// So 8 spindowns cross at 5.6e5 templates (1.47 against 1.11 us at 4.0e5, 1.64
-// against 1.94 at 8.1e5), 16 at 8.7e5 and 24 = 16 + 8 at 1.5e6 (3.64 against
-// 1.96 us at 8.2e5, 3.89 against 3.71 at 1.6e6).  One or two spindowns have no
+//   slice, a barrier and a thread's spindowns per SFT and launch: 1.10 us with
+//   4 per thread, 1.25 with 5, 1.28 with 6 or 7, 1.40 with 8, 2.08 with 16,
+//   summed over the ranges of a split, whose launches follow each other; they
+//   come down to 1.05e-6 us per template.
+// So 8 spindowns cross at 5.9e5 templates (1.43 against 1.04 us at 4.3e5, 1.60
+// against 1.68 at 7.2e5), 16 at 9.0e5 (2.10 against 1.98 at 8.6e5) and 24 =
+// 16 + 8 at 1.5e6 (3.40 against 2.76 us at 1.2e6, 3.39 against 3.52 at 1.55e6);
+// 8 with FP16 coefficients at 1.0e6.  One or two spindowns have no
 // efficient tile (4.1 against 2.2 us at 8e5 templates x 1 spindown, 7.1 against
 // 6.7 at 2.9e6 x 2).  Units whose block of 16 spindowns outgrows the slice keep
 // the tiles: their spindowns share few cache lines.
 bool wave_beats_tile(const fstat_plan* p, const fstat_wu* wu, bool paired) {
   if (resolved_kernel(p) != fstat::KERNEL_INTERP || p->force_seg > 0) return false;
   if (wu->n_fd <= 2) return true;
-  static const double kFloor[17] = {0.0,  0.0, 0.0, 0.0, 1.04, 1.21, 1.29, 1.29, 1.46,
-                                    0.0, 0.0, 0.0, 0.0, 0.0,  0.0,  0.0,  2.17};
+  static const double kFloor[17] = {0.0,  0.0, 0.0, 0.0, 1.10, 1.25, 1.28, 1.28, 1.40,
+                                    0.0, 0.0, 0.0, 0.0, 0.0,  0.0,  0.0,  2.08};
   const FdSplit sp = split_spindowns(wu->n_fd, coef16(p) ? (1u << 8) | (1u << 4) : kAllSplitSizes, paired);
   double tile_us = 0.0;
   for (int i = 0; i < fstat::kSplitSizes; ++i)
     if (sp.n[i] > 0) tile_us += kFloor[fstat::split_nfd(i)];
-  if (coef16(p)) tile_us *= 1.28 / 1.46;
   const double templates = (double)wu->n_sky * (double)wu->n_fd * (double)((wu->n_f + 63) / 64 * 64);
-  return 0.19 + (coef16(p) ? 1.27e-6 : 2.27e-6) * templates < tile_us;
+  return 0.11 + (coef16(p) ? 1.25e-6 : 2.2e-6) * templates < tile_us;
 }
 
 // Turns the completed tile into the wave kernel's where the rule (for the

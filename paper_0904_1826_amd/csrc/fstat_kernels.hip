@@ -1062,9 +1062,7 @@ __device__ __forceinline__ void interp_tile(const WuDev& w, int W, int64_t tile,
     // shift-and-add per pair rather than folding the sign into a subtraction).
     // The reads go through a pointer to the buffer itself, not an address made
     // of an integer: only so does the compiler know that the loads under way
-    // write the other buffer, and not wait for them before the first read
-    // (100 sky points x 64 spindowns x 20000 frequencies x 1000 SFTs: 115.4 ->
-    // 114.3 ms; 18 uneven units in one call: 52.2 -> 51.3 ms).
+    // write the other buffer, and not wait for them before the first read.
     uint32_t boff = __builtin_amdgcn_readfirstlane(0u - 16u * (uint32_t)(k_first + m.lo[kk]));
     __asm__ volatile("" : "+s"(boff));
     // SAFE: an SFT whose windows are not all in the slice reads its
@@ -1261,88 +1259,133 @@ __global__ __launch_bounds__(kThreads, batch_minw(NFD, C16, NSKY)) void demod_in
 // SFT, coefficients read straight from global memory into registers.  What
 // bounds such a unit is the chain of SFTs of a tile (2.1 us per SFT with 16
 // spindowns per thread, of which most is the latency of the staged slice and
-// the barrier), not the vector units, so the wave keeps no LDS slice and no
-// barrier: it loads the coefficients of kAhead SFTs at once while it evaluates
-// the kAhead before them.  The four waves of a work-group take neighbouring
-// spindowns (with w.sky_pairs, two spindowns of each point of a pair) at the
-// same frequencies, whose coefficients share cache lines.  Per template and
-// SFT the arithmetic is that of interp_tile, in the same order, so the results
-// are the same bit for bit.  1 sky point x 51 spindowns x 1801 frequencies x
-// 1500 SFTs: 4.75 ms in tiles (32 work-groups on 256 CUs), 0.48 ms here (0.32
-// us per SFT); 12 x 4 x 700 x 48: 55 and 19 us.  Larger units are bound by the
-// 64 bytes per pair through the vector cache (4.3e11 pairs/s, against 9e11 for
-// full tiles): the host picks per unit.
-constexpr int kAhead = 4;
+// the barrier), not the vector units, so the wave keeps no LDS slice: it loads
+// the coefficients of kAhead SFTs at once while it evaluates the kAhead before
+// them.  The four waves of a work-group take neighbouring spindowns (with
+// w.sky_pairs, two spindowns of each point of a pair) at the same frequencies,
+// whose coefficients share cache lines; a barrier per two groups, with nothing
+// to wait for, keeps them at the same lines.  Per template and SFT the
+// arithmetic is that of interp_tile, in the same order, so the results are the
+// same bit for bit.
+// 1 sky point x 51 spindowns x 1801 frequencies x 1500 SFTs: 4.75 ms in tiles
+// (32 work-groups on 256 CUs), 0.48 ms here (0.32 us per SFT); 8 x 4 x 1800:
+// 0.95 and 0.28 us per SFT; 28 x 1 x 1800: 0.24; 256 templates: 0.28.  Larger
+// units are bound by the 64 bytes per pair through the vector cache (4.5e11
+// pairs/s, against 9e11 for full tiles): the host picks per unit.
+// kAhead: with 4 the register sets take 240 registers, two waves per SIMD: 7 %
+// less at 6e4 templates, but 14 % more at 4e5 (1.18 against 1.04 us per SFT).
+// Through a buffer resource a load costs one shift of address arithmetic (with
+// clamped 64-bit addresses 0.37 us per SFT at 256 templates, 1.13 at 4e5).
+constexpr int kAhead = 2;
 
 // Per-SFT values of one (sky point, spindown), formed by one lane per SFT.
+template <bool SPLIT>
 struct WaveSft {
   double tau, p, q;         // tau, Tdot T, (fdot tau) Tdot T
-  float2 tsplit;            // tau as hi + lo FP32 (split phase mode)
   float2 e;                 // exp(-2 pi i frac(tau (fdot/2) tau))
   float a, b;
+  float2 tsplit[SPLIT];     // tau as hi + lo FP32 (split phase mode)
 };
+
+// The value of SFT lane l of a block: what fetch() loaded, as add() reads it.
+template <bool C16, bool SPLIT>
+struct WaveFetch {
+  double2 g;
+  float a, b;
+  __device__ __forceinline__ void load(const WuDev& w, const double2* geo, const float* arow, const float* brow,
+                                       int al) {
+    g = geo[al];
+    const float sa = C16 ? ldexpf(1.f, w.cexp[al]) : 1.f;         // the FP16 form stores c 2^-e
+    a = C16 ? arow[al] * sa : arow[al];
+    b = C16 ? brow[al] * sa : brow[al];
+  }
+  __device__ __forceinline__ WaveSft<SPLIT> value(double fd) const {
+    WaveSft<SPLIT> x;
+    x.tau = g.x;
+    x.p = g.y;
+    x.q = bin_offset(fd, g.x, g.y);
+    const double h = (0.5 * fd) * g.x;
+    float ph;
+    if constexpr (SPLIT) {
+      x.tsplit[0] = split64(g.x);
+      ph = frac_split_product(x.tsplit[0], split64(h));
+    } else {
+      ph = (float)fract64(g.x * h);
+    }
+    x.e = make_float2(cos_rev(ph), -sin_rev(ph));
+    x.a = a;
+    x.b = b;
+    return x;
+  }
+};
+
+// frac(tau f) of one SFT.
+template <bool SPLIT>
+__device__ __forceinline__ float wave_phase(const WaveSft<SPLIT>& x, double f, float2 fsplit) {
+  if constexpr (SPLIT) return frac_split_product(x.tsplit[0], fsplit);
+  else return (float)fract64(x.tau * f);
+}
+
+__device__ __forceinline__ void wave_store(const WuDev& w, int64_t s, int64_t i, int64_t j, float far, float fai,
+                                           float fbr, float fbi) {
+  const int64_t o = (s * w.n_fd + i) * w.n_f + j;
+  const double4 abcd = w.abcd[s];
+  const double ar = far, ai = fai, br = fbr, bi = fbi;
+  const double fa2 = ar * ar + ai * ai, fb2 = br * br + bi * bi, re = ar * br + ai * bi;
+  const double two_f = 2.0 * (abcd.y * fa2 + abcd.x * fb2 - 2.0 * abcd.z * re) / abcd.w;
+  if (w.twoF) w.twoF[o] = w.accumulate ? w.twoF[o] + (float)two_f : (float)two_f;
+  if (w.cand) cand_push(w, (float)two_f, o);
+  if (w.fa) w.fa[o] = make_float2(far, fai);
+  if (w.fb) w.fb[o] = make_float2(fbr, fbi);
+}
 
 __host__ __device__ constexpr int wave_spindowns(bool pairs, int64_t n_fd) {
   return pairs ? 2 : n_fd >= 3 ? 4 : (int)n_fd;
 }
 
-template <bool C16>
+template <bool C16, bool SPLIT, bool SHARED>
 __global__ __launch_bounds__(kThreads, 3) void demod_wave_kernel(WuDev w) {
-  __shared__ WaveSft lds[kThreads / 64][128];
+  __shared__ WaveSft<SPLIT> lds[kThreads / 64][128];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const bool pairs = w.n_pairs > 0;
+  const bool pairs = SHARED && w.n_pairs > 0;
   const int64_t n_st = pairs ? w.n_pairs : w.n_sky;
   // spindowns per work-group; the other factor of its four waves is the two
   // points of a pair, or neighbouring blocks of 64 frequencies
-  const int per = wave_spindowns(pairs, w.n_fd);
-  const int64_t n_fdb = (w.n_fd + per - 1) / per;
+  const int per = SHARED ? (pairs ? 2 : 4) : (int)w.n_fd;
+  const int64_t n_fdb = SHARED ? (w.n_fd + per - 1) / per : 1;
   int64_t t = blockIdx.x;
   const int64_t st = t % n_st;
   t /= n_st;
   const int64_t i = (t % n_fdb) * per + wv % per;
-  const int64_t j0 = pairs ? (t / n_fdb) * 64 : (t / n_fdb) * (256 / per) + 64 * (wv / per);
+  const int64_t j0 = SHARED ? (t / n_fdb) * 64 : t * (256 / per) + 64 * (wv / per);
   int64_t s = st;
-  bool own = true;                                 // a sky point without a partner is written once
+  // a wave without a template of its own (frequencies or spindowns past the
+  // last, the twin of a sky point without a partner)
+  bool own = i < w.n_fd && j0 < w.n_f;
   if (pairs) {
     const int2 pr = w.sky_pairs[st];
     s = wv & 2 ? pr.y : pr.x;
-    own = !(wv & 2) || pr.x != pr.y;
+    if ((wv & 2) && pr.x == pr.y) own = false;
   }
-  if (i >= w.n_fd || j0 >= w.n_f || !own) return;  // no barrier follows
+  if (!own) return;                                // s_barrier waits for the waves that have not ended
   const int64_t j = j0 + lane < w.n_f ? j0 + lane : w.n_f - 1;
   const double f = template_f(w, j), fd = template_fd(w, i);
   const float2 fsplit = split64(f);
-  const bool split_phase = w.phase_mode != 0;
   const double2* geo = w.geo + s * w.n_sft;
   const float* arow = w.a + s * w.n_sft;
   const float* brow = w.b + s * w.n_sft;
   const int n = (int)w.n_sft, k_first = (int)w.k_first, nb = (int)w.n_bins;
   constexpr int ROWS = C16 ? kRows16 : kCoefPairs;
   typedef typename std::conditional<C16, CoefSet16, CoefSet>::type Set;
-  WaveSft* my = lds[wv];
+  WaveSft<SPLIT>* my = lds[wv];
 
-  double2 g_next;
-  float a_next, b_next;
-  auto fetch = [&](int al0) __attribute__((always_inline)) {      // lane l: the values of SFT al0 + l
-    const int al = al0 + lane < n ? al0 + lane : n - 1;
-    g_next = geo[al];
-    const float sa = C16 ? ldexpf(1.f, w.cexp[al]) : 1.f;         // the FP16 form stores c 2^-e
-    a_next = C16 ? arow[al] * sa : arow[al];
-    b_next = C16 ? brow[al] * sa : brow[al];
+  WaveFetch<C16, SPLIT> next;                      // lane l: the values of SFT al0 + l
+  auto fetch = [&](int al0) __attribute__((always_inline)) {
+    next.load(w, geo, arow, brow, al0 + lane < n ? al0 + lane : n - 1);
   };
   auto publish = [&](int al0) __attribute__((always_inline)) {
-    const double2 g = g_next;
-    WaveSft x;
-    x.tau = g.x;
-    x.p = g.y;
-    x.q = bin_offset(fd, g.x, g.y);
-    x.tsplit = split64(g.x);
-    const double h = (0.5 * fd) * g.x;
-    const float ph = split_phase ? frac_split_product(split64(g.x), split64(h)) : (float)fract64(g.x * h);
-    x.e = make_float2(cos_rev(ph), -sin_rev(ph));
-    x.a = a_next;
-    x.b = b_next;
+    const WaveSft<SPLIT> x = next.value(fd);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     my[(al0 + lane) & 127] = x;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1353,30 +1396,35 @@ __global__ __launch_bounds__(kThreads, 3) void demod_wave_kernel(WuDev w) {
     Set c[kAhead];
     float kap[kAhead];
   };
+  const uint64_t coef = reinterpret_cast<uint64_t>(w.coef);
+  const uint32_t row = 16u * (uint32_t)nb;         // bytes of one coefficient row of an SFT
   auto load = [&](int al0, Group& g) __attribute__((always_inline)) {
 #pragma unroll
     for (int y = 0; y < kAhead; ++y) {
       const int al = al0 + y < n ? al0 + y : n - 1;
-      const WaveSft& x = my[al & 127];
+      const WaveSft<SPLIT>& x = my[al & 127];
       const double dphi = bin_position(f, x.q, x.p);
-      int col = (int)dphi - k_first;
-      col = col < 0 ? 0 : (col >= nb ? nb - 1 : col);             // memory safety only
       g.kap[y] = (float)fract64(dphi);
-      const int64_t base = (int64_t)al * ROWS * nb + col;
+      // a resource over the SFT's rows: an offset beyond them would read 0
+      const uint64_t base = coef + (uint64_t)al * (uint64_t)(ROWS * row);
+      const __amdgpu_buffer_rsrc_t rsrc =
+          __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(base), (short)0, (int)(ROWS * row), 0x00020000);
+      const int off = (int)(16u * (uint32_t)((int)dphi - k_first));
 #pragma unroll
       for (int q = 0; q < ROWS; ++q) {
-        if constexpr (C16) g.c[y].c[q] = reinterpret_cast<const v4f*>(w.coef)[base + (int64_t)q * nb];
-        else g.c[y].c[q] = w.coef[base + (int64_t)q * nb];
+        const v4f v = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, (int)(q * row), 0));
+        if constexpr (C16) g.c[y].c[q] = v;
+        else g.c[y].c[q] = make_float4(v.x, v.y, v.z, v.w);
       }
     }
   };
   float far = 0.f, fai = 0.f, fbr = 0.f, fbi = 0.f;
-  auto add = [&](int al0, const Group& g) __attribute__((always_inline)) {
+  auto add = [&](int al0, const Group& g, auto whole) __attribute__((always_inline)) {
 #pragma unroll
     for (int y = 0; y < kAhead; ++y) {
-      if (al0 + y >= n) break;
-      const WaveSft& x = my[(al0 + y) & 127];
-      const float pf = split_phase ? frac_split_product(x.tsplit, fsplit) : (float)fract64(x.tau * f);
+      if (!decltype(whole)::value && al0 + y >= n) break;
+      const WaveSft<SPLIT>& x = my[(al0 + y) & 127];
+      const float pf = wave_phase(x, f, fsplit);
       const float cf = cos_rev(pf), sf = sin_rev(pf);
       if constexpr (C16)
         interp_accumulate16(g.c[y].c[0], g.c[y].c[1], g.kap[y], cf, sf, x.e, x.a, x.b, far, fai, fbr, fbi);
@@ -1395,25 +1443,27 @@ __global__ __launch_bounds__(kThreads, 3) void demod_wave_kernel(WuDev w) {
   Group ga, gb;
   load(0, ga);
   for (int al = 0; al < n; al += 2 * kAhead) {
+    if (SHARED) __builtin_amdgcn_s_barrier();      // the four waves stay at the same cache lines
     if ((al & 63) == 0 && al + 64 < n) {
       publish(al + 64);
       if (al + 128 < n) fetch(al + 128);
     }
-    if (al + kAhead < n) load(al + kAhead, gb);
-    add(al, ga);
-    if (al + 2 * kAhead < n) load(al + 2 * kAhead, ga);
-    if (al + kAhead < n) add(al + kAhead, gb);
+    if (al + 2 * kAhead <= n) {                    // whole groups: no test between their SFTs
+      load(al + kAhead, gb);
+      __builtin_amdgcn_sched_barrier(0);           // a group's registers are free before the next is loaded
+      add(al, ga, std::true_type{});
+      __builtin_amdgcn_sched_barrier(0);
+      load(al + 2 * kAhead, ga);
+      __builtin_amdgcn_sched_barrier(0);
+      add(al + kAhead, gb, std::true_type{});
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      load(al + kAhead, gb);
+      add(al, ga, std::false_type{});
+      add(al + kAhead, gb, std::false_type{});
+    }
   }
-  if (j0 + lane >= w.n_f) return;
-  const int64_t o = (s * w.n_fd + i) * w.n_f + j;
-  const double4 abcd = w.abcd[s];
-  const double ar = far, ai = fai, br = fbr, bi = fbi;
-  const double fa2 = ar * ar + ai * ai, fb2 = br * br + bi * bi, re = ar * br + ai * bi;
-  const double two_f = 2.0 * (abcd.y * fa2 + abcd.x * fb2 - 2.0 * abcd.z * re) / abcd.w;
-  if (w.twoF) w.twoF[o] = w.accumulate ? w.twoF[o] + (float)two_f : (float)two_f;
-  if (w.cand) cand_push(w, (float)two_f, o);
-  if (w.fa) w.fa[o] = make_float2(far, fai);
-  if (w.fb) w.fb[o] = make_float2(fbr, fbi);
+  if (j0 + lane < w.n_f) wave_store(w, s, i, j, far, fai, fbr, fbi);
 }
 
 // ------------------------------------------------------------ toplist
@@ -1914,18 +1964,27 @@ static hipError_t launch_interp(const WuDev& w, const Tile& t, hipStream_t st) {
 }
 
 // One wave per (sky point, spindown, 64 frequencies), t.wave set.
-static hipError_t launch_wave(const WuDev& w, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+template <bool C16, bool SPLIT>
+static hipError_t launch_wave_t(const WuDev& w, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   const bool pairs = w.n_pairs > 0;
   const int per = wave_spindowns(pairs, w.n_fd);
   const int64_t nf = pairs ? 64 : 256 / per;       // frequencies per work-group
   const int64_t blocks =
       ((w.n_f + nf - 1) / nf) * ((w.n_fd + per - 1) / per) * (pairs ? w.n_pairs : w.n_sky);
   if (blocks <= 0 || blocks > 0x7fffffffLL || (w.n_pairs > 0 && !w.sky_pairs)) return hipErrorInvalidConfiguration;
-  if (w.coef16)
-    hipExtLaunchKernelGGL(demod_wave_kernel<true>, dim3((unsigned)blocks), dim3(kThreads), 0, st, e0, e1, 0, w);
+  if (pairs || w.n_fd >= 3)
+    hipExtLaunchKernelGGL((demod_wave_kernel<C16, SPLIT, true>), dim3((unsigned)blocks), dim3(kThreads), 0, st, e0,
+                          e1, 0, w);
   else
-    hipExtLaunchKernelGGL(demod_wave_kernel<false>, dim3((unsigned)blocks), dim3(kThreads), 0, st, e0, e1, 0, w);
+    hipExtLaunchKernelGGL((demod_wave_kernel<C16, SPLIT, false>), dim3((unsigned)blocks), dim3(kThreads), 0, st, e0,
+                          e1, 0, w);
   return hipGetLastError();
+}
+
+static hipError_t launch_wave(const WuDev& w, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  if (w.coef16)
+    return w.phase_mode ? launch_wave_t<true, true>(w, st, e0, e1) : launch_wave_t<true, false>(w, st, e0, e1);
+  return w.phase_mode ? launch_wave_t<false, true>(w, st, e0, e1) : launch_wave_t<false, false>(w, st, e0, e1);
 }
 
 template <class Seg>

@@ -2,7 +2,7 @@
 instead of interp tiles.  The arithmetic per template and SFT is the tiles',
 in the same order, so 2F, Fa and Fb must equal theirs (forced through the
 tile cache) bit for bit, and the oracle's within its tolerance: around the
-edges of a wave's 64 frequencies, of the groups of 4 SFTs it loads ahead and
+edges of a wave's 64 frequencies, of the groups of SFTs it loads ahead and
 of the blocks of 64 SFTs whose values it keeps in LDS, for every spindown
 count of a work-group's four waves, with and without pairs of sky points."""
 import numpy as np
