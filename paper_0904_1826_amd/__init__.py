@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import dataclasses
+import math
 import os
 from typing import Optional, Sequence
 
@@ -170,15 +171,20 @@ _ELEM = {"f32": ("float32",), "f64": ("float64",), "i32": ("int32",), "i64": ("i
          "u16pair": ("int16", "uint16")}
 
 
+_DTYPE_NAMES = {}         # the dtypes' names: forming one costs more than the rest of a check
+
+
 def _dtype_name(t) -> str:
-    return str(t.dtype).replace("torch.", "")
+    name = _DTYPE_NAMES.get(t.dtype)
+    if name is None:
+        name = str(t.dtype).replace("torch.", "")
+        if len(_DTYPE_NAMES) < 64:
+            _DTYPE_NAMES[t.dtype] = name
+    return name
 
 
 def _numel(t) -> int:
-    n = 1
-    for d in t.shape:
-        n *= int(d)
-    return n
+    return int(math.prod(t.shape))
 
 
 def check_array(name: str, t, kind: str, numel: int, *, at_least: bool = False) -> None:
@@ -237,6 +243,9 @@ def check_output(w, o) -> None:
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
         import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:              # the handle alone: making a Stream object of it takes 3 us
+            return raw(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -296,11 +305,11 @@ def _wu_struct(w) -> fstat_wu:
     off = getattr(w, "det_offset", None)
     keep = None
     if off is not None:                                  # a host array the call reads synchronously
-        vals = [int(x) for x in (off.tolist() if hasattr(off, "tolist") else off)]
+        vals = list(map(int, off.tolist() if hasattr(off, "tolist") else off))
         if len(vals) != int(w.n_det) + 1:
             raise ValueError(f"det_offset: {len(vals)} entries, expected n_det + 1 = {int(w.n_det) + 1}")
         keep = (ctypes.c_int64 * len(vals))(*vals)
-    s = fstat_wu(int(w.n_det), ctypes.cast(keep, ctypes.c_void_p) if keep is not None else None, int(w.n_sft),
+    s = fstat_wu(int(w.n_det), ctypes.addressof(keep) if keep is not None else None, int(w.n_sft),
                  int(w.n_bins), int(w.k_first), float(w.t_sft), _ptr(w.sft), _ptr(w.sft_scale), _ptr(w.t_start),
                  _ptr(w.pos), _ptr(w.vel), int(w.n_sky), _ptr(w.sky), _ptr(w.a), _ptr(w.b), float(w.f0),
                  float(w.df), int(w.n_f), float(w.fdot0), float(w.dfdot), int(w.n_fd), float(w.t_ref),
