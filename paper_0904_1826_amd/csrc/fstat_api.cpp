@@ -107,7 +107,7 @@ struct fstat_plan {
   // persistent grids of the batch kernels with split_nfd(c % kSplitSizes)
   // spindowns and 1 + c / kSplitSizes sky points per tile, with [c][1] and
   // without [c][0] the global-memory fallback
-  int batch_grid[2 * fstat::kSplitSizes][2] = {};
+  int batch_grid[2 * fstat::kSplitSizes][3] = {};
   std::map<std::vector<int64_t>, hipGraphExec_t> graphs;
   // fault injection (host-side forcing of error paths); force_seg > 0 runs the
   // interp kernels without the global-memory path at that slice width
@@ -509,6 +509,21 @@ int interp_seg_tau(const fstat_wu* w, int nfd, int threads, bool c16, double max
   return W & ~3;
 }
 
+// Whether a tile's slots mostly read the bins of the slots before them, so that
+// the form that keeps coefficients from slot to slot is the faster one.  It
+// skips a slot's loads only where no lane of the wave moves to another bin.
+// The lanes' kappa must lie close together: the step times T_sft is a whole
+// number of bins up to the Doppler shift of 64 lanes (1.1e-4 per bin).  With
+// it, neighbouring spindowns move all lanes by |dfdot tau| T_sft bins, at most
+// `shift`, of which the mean is half: at 0.77 (61 % of the loads skipped) a
+// work unit of 1.2e11 pairs takes 109.1 against 114.3 ms, at 0.31 6.00 against
+// 6.59 ms; with lanes apart (a step of 0.37 bins) nothing is skipped and the
+// form costs 3 %.
+bool slots_share(const fstat_wu* w, double max_abs_tau) {
+  const double step = w->df * w->t_sft, shift = fabs(w->dfdot) * max_abs_tau * w->t_sft;
+  return 64.0 * (fabs(step - nearbyint(step)) + 1.1e-4 * fabs(step)) <= 0.25 && shift <= 1.0;
+}
+
 int interp_seg(const fstat_plan* p, const fstat_wu* w, int nfd, int threads, bool* fits) {
   return interp_seg_tau(w, nfd, threads, coef16(p), p->max_abs_tau, p->max_p, fits);
 }
@@ -645,6 +660,7 @@ Tile complete_tile(const fstat_plan* p, const fstat_wu* w, Tile t, bool paired =
         t.fast = t.fast && f;
       }
     }
+    if (t.fast && !coef16(p) && slots_share(w, p->max_abs_tau)) t.fast = fstat::kPathShared;
     if (p->force_seg > 0) {          // fault injection: a slice narrower than the windows need
       t.seg = p->force_seg;
       for (int i = 0; i < fstat::kSplitSizes; ++i) t.seg_split[i] = t.fd_split[i] > 0 ? p->force_seg : 0;
@@ -1258,7 +1274,7 @@ constexpr int kBatchTables = 2 * fstat::kSplitSizes;
 struct BatchTables {
   int mc[kBatchTables] = {}, off[kBatchTables] = {};
   int64_t tiles[kBatchTables] = {};
-  bool fast[kBatchTables] = {};
+  int path[kBatchTables] = {};      // fstat::Path of each launch
 };
 
 int batch_tables(const fstat_plan* p, const fstat_wu* wus, const std::vector<int>& order,
@@ -1270,7 +1286,8 @@ int batch_tables(const fstat_plan* p, const fstat_wu* wus, const std::vector<int
   for (int c = 0; c < kBatchTables; ++c) {
     const int i = c % NS, nsky = 1 + c / NS, nfd = fstat::split_nfd(i);
     tb->off[c] = ne;
-    tb->fast[c] = true;
+    bool fast = true;
+    int64_t shared = 0;                // tiles of units whose slots share coefficients
     for (int q = 0; q < m; ++q) {
       const int k = order[q];
       const bool paired = us[q].pair_width > 0 && nfd <= 8;
@@ -1298,13 +1315,16 @@ int batch_tables(const fstat_plan* p, const fstat_wu* wus, const std::vector<int
         e.seg = p->force_seg;
         fits = true;
       }
-      e.fast = fits ? 1 : 0;
-      tb->fast[c] = tb->fast[c] && fits;
+      fast = fast && fits;
       e.n_tiles = fstat::interp_tiles(e.w, nfd, lo, hi, nsky);
       e.tile_begin = tb->tiles[c];
       tb->tiles[c] += e.n_tiles;
+      if (!coef16(p) && p->force_seg <= 0 && slots_share(&wus[k], status_tau(p->bstat_h[k]))) shared += e.n_tiles;
       ++tb->mc[c];
     }
+    // one form for the whole launch: that of most of its tiles
+    tb->path[c] = !fast ? fstat::kPathSafe : 2 * shared > tb->tiles[c] ? fstat::kPathShared : fstat::kPathFast;
+    for (int q = tb->off[c]; q < tb->off[c] + tb->mc[c]; ++q) eh[q].fast = tb->path[c];
   }
   return ne;
 }
@@ -1393,7 +1413,7 @@ int batch_interp(fstat_plan* p, const fstat_wu* wus, int n, const fstat_out* out
   for (int c = 0; c < NC; ++c) {
     const int nfd = fstat::split_nfd(c % NS), nsky = 1 + c / NS;
     if (!((sizes >> nfd) & 1u) || (nsky == 2 && (!pairing || nfd > 8)) || p->batch_grid[c][0]) continue;
-    for (int sf = 0; sf < 2; ++sf) p->batch_grid[c][sf] = fstat::interp_batch_grid(coef16(p), nfd, sf == 0, nsky);
+    for (int path = 0; path < 3; ++path) p->batch_grid[c][path] = fstat::interp_batch_grid(coef16(p), nfd, path, nsky);
   }
   // sky vectors and pair tables, at each unit's offset in the batch
   std::vector<int64_t> sky_off(n + 1, 0);
@@ -1494,7 +1514,7 @@ int batch_interp(fstat_plan* p, const fstat_wu* wus, int n, const fstat_out* out
     const int* mc = tb.mc;
     const int* off = tb.off;
     const int64_t* tiles = tb.tiles;
-    const bool* fast = tb.fast;
+    const int* path = tb.path;
     e = hipMemcpyAsync(ed + m, eh + m, (size_t)(ne - m) * sizeof(fstat::BatchEntry), hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return hip_err(p, e, "work-unit table upload");
     if (first) {
@@ -1519,8 +1539,8 @@ int batch_interp(fstat_plan* p, const fstat_wu* wus, int n, const fstat_out* out
         const int64_t* q = &bplan[2 * (NC * b + c)];
         if (q[0] == 0) break;
         hipError_t ek = fstat::launch_interp_batch(ed + off[c], (int)q[0], q[1], p->counter + (b * NC + c) * fstat::kXcds,
-                                                   bt.chunk, p->batch_grid[c][fast[c] ? 0 : 1], c16,
-                                                   fstat::split_nfd(c % NS), fast[c], 1 + c / NS,
+                                                   bt.chunk, p->batch_grid[c][path[c]], c16,
+                                                   fstat::split_nfd(c % NS), path[c], 1 + c / NS,
                                                    b * B, (b + 1) * B, s);
         const int r = counted ? check_launch(p, ek, "batch kernel")
                               : (ek == hipSuccess ? FSTAT_OK : hip_err(p, ek, "graph capture"));
@@ -1548,7 +1568,7 @@ int batch_interp(fstat_plan* p, const fstat_wu* wus, int n, const fstat_out* out
     // everything a captured graph holds by value: addresses, counts, kernel variants
     std::vector<int64_t> sig = {(int64_t)(intptr_t)ed, (int64_t)(intptr_t)gcand, (int64_t)(intptr_t)gcount,
                                 m, max_top_k, n_blocks, B, bt.chunk};
-    for (int c = 0; c < NC; ++c) sig.insert(sig.end(), {mc[c], off[c], tiles[c], fast[c] ? 1 : 0});
+    for (int c = 0; c < NC; ++c) sig.insert(sig.end(), {mc[c], off[c], tiles[c], path[c]});
     sig.insert(sig.end(), bplan.begin(), bplan.end());
     auto it = p->graphs.find(sig);
     if (it == p->graphs.end()) {

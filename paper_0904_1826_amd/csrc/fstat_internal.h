@@ -60,6 +60,11 @@ struct WuDev {
 constexpr int kSplitSizes = 6;
 __host__ __device__ constexpr int split_nfd(int i) { return i == 0 ? 16 : 9 - i; }
 
+// Forms of an interp tile: with the global-memory path for SFTs whose windows
+// leave the slice, without it, and without it with the coefficients of a slot
+// kept for the next (slots_shared).
+enum Path : int32_t { kPathSafe = 0, kPathFast = 1, kPathShared = 2 };
+
 // Tile shape of the demodulation kernels.
 struct Tile {
   int32_t nf_reg;   // direct: frequency templates per thread (1, 2 or 4); interp: spindowns per thread
@@ -67,8 +72,8 @@ struct Tile {
   int32_t seg;      // interp: LDS segment width in bins (0: derived)
   int32_t sblock;   // interp: SFTs per launch (the SFT loop is split into launches of this many SFTs)
   int32_t threads;  // interp: work-group size, 64 or 256
-  int32_t fast;     // interp: 1 if the slice holds every window of every SFT (no slice width was capped), so
-                    // the kernel without the global-memory fallback may run
+  int32_t fast;     // interp: Path; kPathFast or kPathShared if the slice holds every window of every SFT (no slice
+                    // width was capped), so the kernel without the global-memory fallback may run
   int32_t pair_seg; // interp: > 0: the ranges of at most 8 spindowns per thread run tiles of two sky points
                     // (WuDev::sky_pairs) with this slice width
   // interp with nf_reg 8, filled by the host for the work unit: the
@@ -113,7 +118,7 @@ struct BatchEntry {
   int32_t seg;
   int32_t nfd;
   int32_t fd_begin, fd_end;
-  int32_t fast;         // the slice holds every window (see Tile::fast)
+  int32_t fast;         // Path of the entry's launch (see Tile::fast)
   int32_t pad;
   int64_t tile_begin;   // first tile in the concatenated tile list
   int64_t n_tiles;
@@ -190,9 +195,9 @@ hipError_t launch_coef_batch(const BatchEntry* ents_dev, int n_ent, int64_t tota
 // (nsky = 2, the entries' WuDev::sky_pairs); other shapes are refused with
 // hipErrorInvalidValue.
 hipError_t launch_interp_batch(const BatchEntry* ents_dev, int n_ent, int64_t total_tiles,
-                               unsigned long long* counters, int64_t chunk, int grid, bool c16, int nfd, bool fast,
+                               unsigned long long* counters, int64_t chunk, int grid, bool c16, int nfd, int path,
                                int nsky, int64_t al0, int64_t al1, hipStream_t s);
-int interp_batch_grid(bool c16, int nfd, bool fast, int nsky);
+int interp_batch_grid(bool c16, int nfd, int path, int nsky);
 hipError_t launch_bins(const WuDev& w, int64_t n, const int32_t* i_sky, const int32_t* i_fd, const int32_t* i_f,
                        const int32_t* i_sft, int64_t* kstar, double* kappa, double* phi_frac, hipStream_t s);
 int interp_max_seg(int threads, bool c16);

@@ -926,6 +926,81 @@ __device__ __forceinline__ void interp_accumulate16(v4f r0, v4f r1, float u, flo
 }
 
 __device__ __forceinline__ v4f lds_load_v(LdsPtr p, int i) { return p[i]; }
+__device__ __forceinline__ float4 f4(v4f v) { return make_float4(v.x, v.y, v.z, v.w); }
+
+__device__ __forceinline__ void lgkm_wait() { __builtin_amdgcn_s_waitcnt(0xC07F); }   // lgkmcnt(0)
+
+// The slots (sky point u, spindown r) of one SFT for a tile whose slots mostly
+// read the same bins (slots_share).  What bounds the plain loop is LDS: 64
+// bytes of coefficients per pair, 128 per clock and CU, are read at 96 % of
+// that rate, and the multiply-adds (two waves' per SIMD run side by side
+// where no operand is scalar) would take two thirds of the time.  So a slot
+// keeps the coefficients of the slot before it in its chain where no lane of
+// the wave moved to another bin.  Two chains (the sky points of a pair, or the
+// halves of the spindowns) alternate: the next slot of one is loaded while the
+// other is evaluated, 16 registers each.  The empty asm statements hold every
+// slot's arithmetic in its place (the compiler would sink it past the
+// branches) and a row's four registers together.  Same arithmetic, same order
+// as the plain loop.  Measured (plain, shared): 2000 sky points x 8 spindowns
+// x 3600 frequencies x 2000 SFTs 114.3, 109.1 ms (61 % of the loads left
+// out); 40 x 32 x 14400 x 2200 in batches 99.2, 90.3 ms; 301 x 8 x 2701 x 801
+// 6.59, 6.00 ms.
+template <int NFD, int NSKY, bool C16>
+__device__ __forceinline__ void slots_shared(const double (&mg)[NSKY][NFD], const float2 (&me)[NSKY][NFD],
+                                             const float4* seg, uint32_t boff, int Wp, double f, const double* pu,
+                                             const float* cf, const float* sf, const float* au, const float* bu,
+                                             float* far, float* fai, float* fbr, float* fbi) {
+  static_assert(!C16, "FP16 coefficients: half the bytes, the plain loop is not bound by them");
+  constexpr int NSL = NSKY * NFD;
+  constexpr int H = NSKY == 2 ? NFD : (NFD + 1) / 2;         // slots of the longer chain
+  auto slot = [](int t) { return (t & 1) * H + (t >> 1); };  // slot t of the loop belongs to chain t % 2
+  v4f c[2][kCoefPairs];
+  uint32_t at[2] = {0u, 0u};
+  float kap[2];
+  double g[3];
+  float2 e[3];
+  auto values = [&](int t) __attribute__((always_inline)) {
+    const int x = slot(t);
+    g[t % 3] = mg[x / NFD][x % NFD];
+    e[t % 3] = me[x / NFD][x % NFD];
+  };
+  auto fetch = [&](int t) __attribute__((always_inline)) {
+    const double dphi = bin_position(f, g[t % 3], pu[slot(t) / NFD]);
+    const uint32_t a = ((uint32_t)(int)dphi << 4) + boff;
+    kap[t & 1] = (float)fract64(dphi);
+    if (t < 2 || __builtin_amdgcn_ballot_w64(a != at[t & 1])) {
+      const LdsPtr q = lds_at(seg, a);
+#pragma unroll
+      for (int y = 0; y < kCoefPairs; ++y) c[t & 1][y] = lds_load_v(q, y * Wp);
+    }
+    at[t & 1] = a;
+  };
+  values(0);
+  values(1);
+  values(2);
+  fetch(0);
+  fetch(1);
+  lgkm_wait();
+#pragma unroll
+  for (int t = 0; t < 2 * H; ++t) {
+    const int x = slot(t), u = x / NFD;
+    if (x >= NSL) continue;
+    v4f* q = c[t & 1];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int y = 0; y < kCoefPairs; ++y) __asm__ volatile("" : "+v"(q[y]));
+    interp_accumulate(f4(q[0]), f4(q[1]), f4(q[2]), f4(q[3]), kap[t & 1], cf[u], sf[u], e[t % 3], au[u], bu[u], far[x],
+                      fai[x], fbr[x], fbi[x]);
+    __asm__ volatile("" : "+v"(far[x]), "+v"(fai[x]), "+v"(fbr[x]), "+v"(fbi[x]));
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + 2 < 2 * H && slot(t + 2) < NSL) {
+      lgkm_wait();                                 // slot t + 1's coefficients, slot t + 2's values
+      fetch(t + 2);
+      if (t + 3 < 2 * H && slot(t + 3) < NSL) values(t + 3);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
 
 // Demodulation over SFTs [al_begin, al_end) for tiles of (sky s, NFD
 // spindowns, NT frequencies), sky point fastest, one tile per work-group.
@@ -949,10 +1024,11 @@ __device__ __forceinline__ v4f lds_load_v(LdsPtr p, int i) { return p[i]; }
 // The tile covers spindowns [fd0, fd1) of the work unit in blocks of NFD
 // (the last block of a range may be partial: its missing spindowns repeat
 // the range's last one and are not written).
-template <int NFD, int S, int G, int NT, bool C16, bool SAFE, int NSKY = 1>
+template <int NFD, int S, int G, int NT, bool C16, int PATH, int NSKY = 1>
 __device__ __forceinline__ void interp_tile(const WuDev& w, int W, int64_t tile, int64_t al_begin, int64_t al_end,
                                             float4* cbuf0, float4* cbuf1, GroupMeta<NFD, S, NSKY>* meta, int64_t fd0,
                                             int64_t fd1) {
+  constexpr bool SAFE = PATH == kPathSafe, SHARE = PATH == kPathShared;
   const int tid = threadIdx.x;
   const int64_t n_fdb = (fd1 - fd0 + NFD - 1) / NFD;
   using F = SliceForm<NT, C16>;
@@ -1073,6 +1149,9 @@ __device__ __forceinline__ void interp_tile(const WuDev& w, int W, int64_t tile,
     // flag stays a run-time branch: with the test folded away the compiler
     // schedules across SFTs and spills.
     if (__builtin_amdgcn_readfirstlane(m.fast[kk])) {
+      if constexpr (SHARE) {
+        slots_shared<NFD, NSKY, C16>(m.g[kk], m.e[kk], seg, boff, Wp, f, pu, cf, sf, au, bu, far, fai, fbr, fbi);
+      } else {
 #pragma unroll
       for (int x = 0; x < NSL; ++x) {
         const int u = x / NFD, r = x % NFD;
@@ -1086,6 +1165,7 @@ __device__ __forceinline__ void interp_tile(const WuDev& w, int W, int64_t tile,
           interp_accumulate(lds_load(c, 0), lds_load(c, Wp), lds_load(c, 2 * Wp), lds_load(c, 3 * Wp), kap, cf[u],
                             sf[u], m.e[kk][u][r], au[u], bu[u], far[x], fai[x], fbr[x], fbi[x]);
         if (x % G == G - 1) __builtin_amdgcn_sched_barrier(0);   // bounds the coefficient registers in flight
+      }
       }
     } else if constexpr (SAFE) {
 #pragma unroll
@@ -1155,14 +1235,14 @@ __device__ __forceinline__ void interp_tile(const WuDev& w, int W, int64_t tile,
 }
 
 // One tile per work-group (see interp_tile) over spindowns [fd0, fd1).
-template <int NFD, int S, int MINW, int G, int NT, bool C16, bool SAFE, int NSKY = 1>
+template <int NFD, int S, int MINW, int G, int NT, bool C16, int PATH, int NSKY = 1>
 __global__ __launch_bounds__(NT, MINW) void demod_interp_kernel(WuDev w, int W, int64_t al_begin, int64_t al_end,
                                                                  int64_t fd0, int64_t fd1) {
   using F = SliceForm<NT, C16>;
   __shared__ GroupMeta<NFD, S, NSKY> meta[2];
   __shared__ float4 cbuf0[F::rows * F::cap];
   __shared__ float4 cbuf1[F::rows * F::cap];
-  interp_tile<NFD, S, G, NT, C16, SAFE, NSKY>(w, W, blockIdx.x, al_begin, al_end, cbuf0, cbuf1, meta, fd0, fd1);
+  interp_tile<NFD, S, G, NT, C16, PATH, NSKY>(w, W, blockIdx.x, al_begin, al_end, cbuf0, cbuf1, meta, fd0, fd1);
 }
 
 // Many work units in one persistent launch: the grid holds as many
@@ -1194,7 +1274,7 @@ __host__ __device__ constexpr int batch_minw(int nfd, bool c16, int nsky) {
   return nfd == 16 ? 3 : nsky == 2 ? (nfd <= 4 ? 4 : 3) : nfd == 8 ? (c16 ? 5 : 4) : (nfd >= 5 ? 4 : 3);
 }
 
-template <int NFD, bool C16, bool SAFE, int NSKY = 1>
+template <int NFD, bool C16, int PATH, int NSKY = 1>
 __global__ __launch_bounds__(kThreads, batch_minw(NFD, C16, NSKY)) void demod_interp_batch_kernel(
     const BatchEntry* __restrict__ ents, int n_ent, int64_t total_tiles, unsigned long long* counters, int64_t chunk,
     int64_t al0, int64_t al1) {
@@ -1247,7 +1327,7 @@ __global__ __launch_bounds__(kThreads, batch_minw(NFD, C16, NSKY)) void demod_in
     const int64_t al_end = w.n_sft < al1 ? w.n_sft : al1;
     // tiles of two sky points keep two slots' coefficients in flight (four
     // with one): the queue loop's registers on top of 2 NFD accumulator sets
-    interp_tile<NFD, S, NSKY == 2 ? 2 : 4, kThreads, C16, SAFE, NSKY>(w, W, local, al0, al_end, cbuf0, cbuf1, meta,
+    interp_tile<NFD, S, NSKY == 2 ? 2 : 4, kThreads, C16, PATH, NSKY>(w, W, local, al0, al_end, cbuf0, cbuf1, meta,
                                                                      ents[lo].fd_begin, ents[lo].fd_end);
     __syncthreads();                                 // LDS free for the next tile
   }
@@ -1737,85 +1817,94 @@ int64_t interp_tiles(const WuDev& w, int nfd, int64_t fd0, int64_t fd1, int nsky
   return ((w.n_f + kThreads - 1) / kThreads) * ((fd1 - fd0 + nfd - 1) / nfd) * (nsky == 2 ? w.n_pairs : w.n_sky);
 }
 
-template <int NFD, bool C16, bool SAFE, int NSKY = 1>
+template <int NFD, bool C16, int PATH, int NSKY = 1>
 static int batch_grid_t(int cus) {
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, demod_interp_batch_kernel<NFD, C16, SAFE, NSKY>,
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, demod_interp_batch_kernel<NFD, C16, PATH, NSKY>,
                                                    kThreads, 0) != hipSuccess ||
       per_cu < 1)
     per_cu = 1;
   return per_cu * cus;
 }
 
-int interp_batch_grid(bool c16, int nfd, bool fast, int nsky) {
+template <int NFD, int NSKY = 1>
+static int batch_grid_of(int path, int cus) {
+  return path == kPathShared ? batch_grid_t<NFD, false, kPathShared, NSKY>(cus)
+         : path == kPathFast ? batch_grid_t<NFD, false, kPathFast, NSKY>(cus)
+                             : batch_grid_t<NFD, false, kPathSafe, NSKY>(cus);
+}
+
+int interp_batch_grid(bool c16, int nfd, int path, int nsky) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     cus = 256;
   if (nsky == 2 && !c16) {
     switch (nfd) {
-      case 8: return fast ? batch_grid_t<8, false, false, 2>(cus) : batch_grid_t<8, false, true, 2>(cus);
-      case 7: return fast ? batch_grid_t<7, false, false, 2>(cus) : batch_grid_t<7, false, true, 2>(cus);
-      case 6: return fast ? batch_grid_t<6, false, false, 2>(cus) : batch_grid_t<6, false, true, 2>(cus);
-      case 5: return fast ? batch_grid_t<5, false, false, 2>(cus) : batch_grid_t<5, false, true, 2>(cus);
-      default: return fast ? batch_grid_t<4, false, false, 2>(cus) : batch_grid_t<4, false, true, 2>(cus);
+      case 8: return batch_grid_of<8, 2>(path, cus);
+      case 7: return batch_grid_of<7, 2>(path, cus);
+      case 6: return batch_grid_of<6, 2>(path, cus);
+      case 5: return batch_grid_of<5, 2>(path, cus);
+      default: return batch_grid_of<4, 2>(path, cus);
     }
   }
   if (c16) {
-    if (nfd == 8) return fast ? batch_grid_t<8, true, false>(cus) : batch_grid_t<8, true, true>(cus);
-    return fast ? batch_grid_t<4, true, false>(cus) : batch_grid_t<4, true, true>(cus);
+    if (nfd == 8) return path != kPathSafe ? batch_grid_t<8, true, kPathFast>(cus) : batch_grid_t<8, true, kPathSafe>(cus);
+    return path != kPathSafe ? batch_grid_t<4, true, kPathFast>(cus) : batch_grid_t<4, true, kPathSafe>(cus);
   }
   switch (nfd) {
-    case 16: return fast ? batch_grid_t<16, false, false>(cus) : batch_grid_t<16, false, true>(cus);
-    case 8: return fast ? batch_grid_t<8, false, false>(cus) : batch_grid_t<8, false, true>(cus);
-    case 7: return fast ? batch_grid_t<7, false, false>(cus) : batch_grid_t<7, false, true>(cus);
-    case 6: return fast ? batch_grid_t<6, false, false>(cus) : batch_grid_t<6, false, true>(cus);
-    case 5: return fast ? batch_grid_t<5, false, false>(cus) : batch_grid_t<5, false, true>(cus);
-    default: return fast ? batch_grid_t<4, false, false>(cus) : batch_grid_t<4, false, true>(cus);
+    case 16: return batch_grid_of<16>(path, cus);
+    case 8: return batch_grid_of<8>(path, cus);
+    case 7: return batch_grid_of<7>(path, cus);
+    case 6: return batch_grid_of<6>(path, cus);
+    case 5: return batch_grid_of<5>(path, cus);
+    default: return batch_grid_of<4>(path, cus);
   }
 }
 
 hipError_t launch_interp_batch(const BatchEntry* ents_dev, int n_ent, int64_t total_tiles,
-                               unsigned long long* counters, int64_t chunk, int grid, bool c16, int nfd, bool fast,
+                               unsigned long long* counters, int64_t chunk, int grid, bool c16, int nfd, int path,
                                int nsky, int64_t al0, int64_t al1, hipStream_t st) {
   if (n_ent <= 0 || total_tiles <= 0) return hipSuccess;
   if (al0 < 0 || al1 <= al0 || chunk < 1) return hipErrorInvalidValue;
   if (c16 ? (nfd != 8 && nfd != 4) : ((nfd < 4 || nfd > 8) && nfd != 16)) return hipErrorInvalidValue;
   if (nsky != 1 && (nsky != 2 || c16 || nfd > 8)) return hipErrorInvalidValue;
   const dim3 g((unsigned)grid), b(kThreads);
-#define FSTAT_BATCH_LAUNCH(N, C, SF) \
-  hipLaunchKernelGGL((demod_interp_batch_kernel<N, C, SF>), g, b, 0, st, ents_dev, n_ent, total_tiles, counters, \
+#define FSTAT_BATCH_LAUNCH(N, C, P, K) \
+  hipLaunchKernelGGL((demod_interp_batch_kernel<N, C, P, K>), g, b, 0, st, ents_dev, n_ent, total_tiles, counters, \
                      chunk, al0, al1)
-#define FSTAT_BATCH_LAUNCH2(N, C) \
-  do { if (fast) FSTAT_BATCH_LAUNCH(N, C, false); else FSTAT_BATCH_LAUNCH(N, C, true); } while (0)
-#define FSTAT_BATCH_LAUNCH_P(N) \
+#define FSTAT_BATCH_LAUNCH2(N, K) \
   do { \
-    if (fast) hipLaunchKernelGGL((demod_interp_batch_kernel<N, false, false, 2>), g, b, 0, st, ents_dev, n_ent, \
-                                 total_tiles, counters, chunk, al0, al1); \
-    else hipLaunchKernelGGL((demod_interp_batch_kernel<N, false, true, 2>), g, b, 0, st, ents_dev, n_ent, \
-                            total_tiles, counters, chunk, al0, al1); \
+    if (path == kPathShared) FSTAT_BATCH_LAUNCH(N, false, kPathShared, K); \
+    else if (path == kPathFast) FSTAT_BATCH_LAUNCH(N, false, kPathFast, K); \
+    else FSTAT_BATCH_LAUNCH(N, false, kPathSafe, K); \
+  } while (0)
+#define FSTAT_BATCH_LAUNCH_C16(N) \
+  do { \
+    if (path != kPathSafe) FSTAT_BATCH_LAUNCH(N, true, kPathFast, 1); \
+    else FSTAT_BATCH_LAUNCH(N, true, kPathSafe, 1); \
   } while (0)
   if (nsky == 2) {
     switch (nfd) {
-      case 8: FSTAT_BATCH_LAUNCH_P(8); break;
-      case 7: FSTAT_BATCH_LAUNCH_P(7); break;
-      case 6: FSTAT_BATCH_LAUNCH_P(6); break;
-      case 5: FSTAT_BATCH_LAUNCH_P(5); break;
-      default: FSTAT_BATCH_LAUNCH_P(4); break;
+      case 8: FSTAT_BATCH_LAUNCH2(8, 2); break;
+      case 7: FSTAT_BATCH_LAUNCH2(7, 2); break;
+      case 6: FSTAT_BATCH_LAUNCH2(6, 2); break;
+      case 5: FSTAT_BATCH_LAUNCH2(5, 2); break;
+      default: FSTAT_BATCH_LAUNCH2(4, 2); break;
     }
   } else if (c16) {
-    if (nfd == 8) FSTAT_BATCH_LAUNCH2(8, true);
-    else FSTAT_BATCH_LAUNCH2(4, true);
+    if (nfd == 8) FSTAT_BATCH_LAUNCH_C16(8);
+    else FSTAT_BATCH_LAUNCH_C16(4);
   } else {
     switch (nfd) {
-      case 16: FSTAT_BATCH_LAUNCH2(16, false); break;
-      case 8: FSTAT_BATCH_LAUNCH2(8, false); break;
-      case 7: FSTAT_BATCH_LAUNCH2(7, false); break;
-      case 6: FSTAT_BATCH_LAUNCH2(6, false); break;
-      case 5: FSTAT_BATCH_LAUNCH2(5, false); break;
-      default: FSTAT_BATCH_LAUNCH2(4, false); break;
+      case 16: FSTAT_BATCH_LAUNCH2(16, 1); break;
+      case 8: FSTAT_BATCH_LAUNCH2(8, 1); break;
+      case 7: FSTAT_BATCH_LAUNCH2(7, 1); break;
+      case 6: FSTAT_BATCH_LAUNCH2(6, 1); break;
+      case 5: FSTAT_BATCH_LAUNCH2(5, 1); break;
+      default: FSTAT_BATCH_LAUNCH2(4, 1); break;
     }
   }
-#undef FSTAT_BATCH_LAUNCH_P
+#undef FSTAT_BATCH_LAUNCH_C16
 #undef FSTAT_BATCH_LAUNCH2
 #undef FSTAT_BATCH_LAUNCH
   return hipGetLastError();
@@ -1826,7 +1915,7 @@ int interp_launches(const WuDev& w, const Tile& t) {
   return (int)((w.n_sft + sb - 1) / sb);
 }
 
-template <int NFD, int S, int MINW, int G, int NT, bool C16, bool SAFE = true, int NSKY = 1>
+template <int NFD, int S, int MINW, int G, int NT, bool C16, int PATH = kPathSafe, int NSKY = 1>
 static hipError_t launch_interp_t(const WuDev& w, const Tile& t, hipStream_t st, int64_t fd0, int64_t fd1) {
   const int W = t.seg;
   const int64_t n_ft = (w.n_f + NT - 1) / NT;
@@ -1838,12 +1927,19 @@ static hipError_t launch_interp_t(const WuDev& w, const Tile& t, hipStream_t st,
   if (sb < w.n_sft && !w.acc) return hipErrorInvalidValue;
   for (int64_t al = 0; al < w.n_sft; al += sb) {
     const int64_t end = al + sb < w.n_sft ? al + sb : w.n_sft;
-    hipLaunchKernelGGL((demod_interp_kernel<NFD, S, MINW, G, NT, C16, SAFE, NSKY>), dim3((unsigned)n_tiles), dim3(NT),
+    hipLaunchKernelGGL((demod_interp_kernel<NFD, S, MINW, G, NT, C16, PATH, NSKY>), dim3((unsigned)n_tiles), dim3(NT),
                        0, st, w, W, al, end, fd0, fd1);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// The fast form of an FP32 tile, with or without shared coefficients.
+template <int NFD, int S, int MINW, int G, int NSKY = 1>
+static hipError_t launch_fast_t(const WuDev& w, const Tile& t, hipStream_t st, int64_t fd0, int64_t fd1) {
+  return t.fast == kPathShared ? launch_interp_t<NFD, S, MINW, G, kThreads, false, kPathShared, NSKY>(w, t, st, fd0, fd1)
+                               : launch_interp_t<NFD, S, MINW, G, kThreads, false, kPathFast, NSKY>(w, t, st, fd0, fd1);
 }
 
 int interp_max_seg(int threads, bool c16) {
@@ -1862,12 +1958,12 @@ static hipError_t launch_interp_range(const WuDev& w, const Tile& t, hipStream_t
   if (w.coef16) {
     if (t.threads == 64) return hipErrorInvalidValue;
     switch (t.nf_reg) {
-      case 8: return t.chunk >= 5 ? (t.fast ? launch_interp_t<8, 16, 5, 4, kThreads, true, false>(w, t, st, fd0, fd1)
+      case 8: return t.chunk >= 5 ? (t.fast ? launch_interp_t<8, 16, 5, 4, kThreads, true, kPathFast>(w, t, st, fd0, fd1)
                                             : launch_interp_t<8, 16, 5, 4, kThreads, true>(w, t, st, fd0, fd1))
                    : t.chunk >= 4 ? launch_interp_t<8, 16, 4, 4, kThreads, true>(w, t, st, fd0, fd1)
                      : w3         ? launch_interp_t<8, 16, 3, 4, kThreads, true>(w, t, st, fd0, fd1)
                                   : launch_interp_t<8, 16, 2, 4, kThreads, true>(w, t, st, fd0, fd1);
-      case 4: return w3 ? (t.fast ? launch_interp_t<4, 16, 3, 4, kThreads, true, false>(w, t, st, fd0, fd1)
+      case 4: return w3 ? (t.fast ? launch_interp_t<4, 16, 3, 4, kThreads, true, kPathFast>(w, t, st, fd0, fd1)
                                   : launch_interp_t<4, 16, 3, 4, kThreads, true>(w, t, st, fd0, fd1))
                         : launch_interp_t<4, 16, 2, 4, kThreads, true>(w, t, st, fd0, fd1);
       case 2: return launch_interp_t<2, 16, 3, 4, kThreads, true>(w, t, st, fd0, fd1);
@@ -1891,36 +1987,36 @@ static hipError_t launch_interp_range(const WuDev& w, const Tile& t, hipStream_t
     // tiles of two sky points (t.pair_seg > 0): 16 accumulator slots per
     // thread, three waves per SIMD
     case 8: if (t.pair_seg > 0)
-              return t.fast ? launch_interp_t<8, 8, 3, 4, kThreads, false, false, 2>(w, t, st, fd0, fd1)
-                            : launch_interp_t<8, 8, 3, 4, kThreads, false, true, 2>(w, t, st, fd0, fd1);
-            return t.chunk >= 4 ? (t.fast ? launch_interp_t<8, 8, 4, 4, kThreads, false, false>(w, t, st, fd0, fd1)
+              return t.fast ? launch_fast_t<8, 8, 3, 4, 2>(w, t, st, fd0, fd1)
+                            : launch_interp_t<8, 8, 3, 4, kThreads, false, kPathSafe, 2>(w, t, st, fd0, fd1);
+            return t.chunk >= 4 ? (t.fast ? launch_fast_t<8, 8, 4, 4>(w, t, st, fd0, fd1)
                                           : launch_interp_t<8, 8, 4, 4, kThreads, false>(w, t, st, fd0, fd1))
                    : w3         ? launch_interp_t<8, 16, 3, 4, kThreads, false>(w, t, st, fd0, fd1)
                                 : launch_interp_t<8, 16, 2, 4, kThreads, false>(w, t, st, fd0, fd1);
     // 16 and 7 to 5: ranges of a split 8-spindown tile (three waves per SIMD
     // for 16, four for the others); ranges of 4 to 7 with tiles of two sky
     // points (t.pair_seg > 0) have their own specialisations
-    case 16: return t.fast ? launch_interp_t<16, 8, 3, 4, kThreads, false, false>(w, t, st, fd0, fd1)
+    case 16: return t.fast ? launch_fast_t<16, 8, 3, 4>(w, t, st, fd0, fd1)
                            : launch_interp_t<16, 8, 3, 4, kThreads, false>(w, t, st, fd0, fd1);
     case 7: if (t.pair_seg > 0)
-              return t.fast ? launch_interp_t<7, 8, 3, 4, kThreads, false, false, 2>(w, t, st, fd0, fd1)
-                            : launch_interp_t<7, 8, 3, 4, kThreads, false, true, 2>(w, t, st, fd0, fd1);
-            return t.fast ? launch_interp_t<7, 8, 4, 4, kThreads, false, false>(w, t, st, fd0, fd1)
+              return t.fast ? launch_fast_t<7, 8, 3, 4, 2>(w, t, st, fd0, fd1)
+                            : launch_interp_t<7, 8, 3, 4, kThreads, false, kPathSafe, 2>(w, t, st, fd0, fd1);
+            return t.fast ? launch_fast_t<7, 8, 4, 4>(w, t, st, fd0, fd1)
                           : launch_interp_t<7, 8, 4, 4, kThreads, false>(w, t, st, fd0, fd1);
     case 6: if (t.pair_seg > 0)
-              return t.fast ? launch_interp_t<6, 8, 3, 4, kThreads, false, false, 2>(w, t, st, fd0, fd1)
-                            : launch_interp_t<6, 8, 3, 4, kThreads, false, true, 2>(w, t, st, fd0, fd1);
-            return t.fast ? launch_interp_t<6, 8, 4, 4, kThreads, false, false>(w, t, st, fd0, fd1)
+              return t.fast ? launch_fast_t<6, 8, 3, 4, 2>(w, t, st, fd0, fd1)
+                            : launch_interp_t<6, 8, 3, 4, kThreads, false, kPathSafe, 2>(w, t, st, fd0, fd1);
+            return t.fast ? launch_fast_t<6, 8, 4, 4>(w, t, st, fd0, fd1)
                           : launch_interp_t<6, 8, 4, 4, kThreads, false>(w, t, st, fd0, fd1);
     case 5: if (t.pair_seg > 0)
-              return t.fast ? launch_interp_t<5, 8, 3, 4, kThreads, false, false, 2>(w, t, st, fd0, fd1)
-                            : launch_interp_t<5, 8, 3, 4, kThreads, false, true, 2>(w, t, st, fd0, fd1);
-            return t.fast ? launch_interp_t<5, 8, 4, 4, kThreads, false, false>(w, t, st, fd0, fd1)
+              return t.fast ? launch_fast_t<5, 8, 3, 4, 2>(w, t, st, fd0, fd1)
+                            : launch_interp_t<5, 8, 3, 4, kThreads, false, kPathSafe, 2>(w, t, st, fd0, fd1);
+            return t.fast ? launch_fast_t<5, 8, 4, 4>(w, t, st, fd0, fd1)
                           : launch_interp_t<5, 8, 4, 4, kThreads, false>(w, t, st, fd0, fd1);
     case 4: if (t.pair_seg > 0)        // 4 groups of per-SFT values: four work-groups' LDS fits a CU
-              return t.fast ? launch_interp_t<4, 4, 4, 4, kThreads, false, false, 2>(w, t, st, fd0, fd1)
-                            : launch_interp_t<4, 4, 4, 4, kThreads, false, true, 2>(w, t, st, fd0, fd1);
-            return w3 ? (t.fast ? launch_interp_t<4, 16, 3, 4, kThreads, false, false>(w, t, st, fd0, fd1)
+              return t.fast ? launch_fast_t<4, 4, 4, 4, 2>(w, t, st, fd0, fd1)
+                            : launch_interp_t<4, 4, 4, 4, kThreads, false, kPathSafe, 2>(w, t, st, fd0, fd1);
+            return w3 ? (t.fast ? launch_fast_t<4, 16, 3, 4>(w, t, st, fd0, fd1)
                                 : launch_interp_t<4, 16, 3, 4, kThreads, false>(w, t, st, fd0, fd1))
                       : launch_interp_t<4, 16, 2, 4, kThreads, false>(w, t, st, fd0, fd1);
     case 2: return launch_interp_t<2, 16, 3, 4, kThreads, false>(w, t, st, fd0, fd1);
