@@ -521,7 +521,8 @@ int interp_seg_tau(const fstat_wu* w, int nfd, int threads, bool c16, double max
 // form costs 3 %.
 bool slots_share(const fstat_wu* w, double max_abs_tau) {
   const double step = w->df * w->t_sft, shift = fabs(w->dfdot) * max_abs_tau * w->t_sft;
-  return 64.0 * (fabs(step - nearbyint(step)) + 1.1e-4 * fabs(step)) <= 0.25 && shift <= 1.0;
+  return 64.0 * (fabs(step - nearbyint(step)) + 1.1e-4 * fabs(step)) <= 0.25 && shift <= 1.0 &&
+         w->n_bins < (1 << 20);          // the form reads columns from the position's high word
 }
 
 int interp_seg(const fstat_plan* p, const fstat_wu* w, int nfd, int threads, bool* fits) {
