@@ -1087,6 +1087,40 @@ bool pairs_apply(const fstat_plan* p, const fstat_wu* wu, const Tile& t) {
          t.chunk >= 4 && wu->n_sky >= 4 && p->force_seg <= 0;
 }
 
+bool wave_beats_tile(const fstat_plan* p, const fstat_wu* wu, bool paired);
+
+// Tiles of two sky points take 1.91 times as long per SFT as tiles of one
+// (2000 sky points x 8 spindowns x 3600 frequencies x 400 SFTs, all of them
+// paired: 20.0 against 21.1 ms), 1.80 in the form that shares no coefficients
+// (1000 x 5 x 3600 x 400 at a step of 0.37 bins: 8.15 against 8.79 ms), so they
+// pay if few points go without a partner.
+double pair_cost(bool shared) { return shared ? 1.91 : 1.80; }
+bool pairs_pay(int64_t np, int64_t n, bool shared) { return pair_cost(shared) * (double)np <= (double)n; }
+
+// Time of a completed tile's launches in the time of one (sky point, spindown)
+// slot on a full device: the work-groups run in rounds of `per` on each of the
+// 256 CUs, and a last round of k of them takes about 0.2 + 0.8 k / per of a
+// full one, since what is left runs faster with fewer beside it.  Measured
+// (paired, single; 400 SFTs, 8 spindowns): 150 sky points x 3600 frequencies,
+// 1125 paired work-groups, 2.06, 1.96 ms (model: +5 %); 200, 2.31, 2.43 (-4 %);
+// 350, 4.07, 4.05 (0 %); 61 x 5 spindowns x 3001 x 701 SFTs, 372, 1.35, 1.09.
+double grid_slots(const fstat_wu* wu, const Tile& t, int64_t np) {
+  const int64_t n_ft = (wu->n_f + fstat::kThreads - 1) / fstat::kThreads;
+  const bool one = std::all_of(t.fd_split, t.fd_split + fstat::kSplitSizes, [](int32_t x) { return x == 0; });
+  double sum = 0.0;
+  for (int i = 0; i < fstat::kSplitSizes; ++i) {
+    const int nfd = fstat::split_nfd(i);
+    const int64_t n = one ? (nfd == 8 ? wu->n_fd : 0) : t.fd_split[i];
+    if (n <= 0) continue;
+    const bool pair = np > 0 && nfd <= 8;
+    const int64_t round = 256 * (pair ? (nfd == 4 ? 4 : 3) : nfd == 16 ? 3 : 4);
+    const int64_t groups = n_ft * ((n + nfd - 1) / nfd) * (pair ? np : wu->n_sky);
+    const double tail = groups % round ? 0.2 + 0.8 * (double)((groups % round + 255) / 256 * 256) / (double)round : 0.0;
+    sum += ((double)(groups / round) + tail) * (double)round * nfd * (pair ? pair_cost(t.fast == fstat::kPathShared) : 1.0);
+  }
+  return sum;
+}
+
 // The pairing itself, from a host copy of the sky vectors and the unit's
 // geometry status; the table goes to pairs_h and is uploaded to pairs_d
 // (room for n_sky entries each).
@@ -1103,6 +1137,8 @@ int pair_sky(fstat_plan* p, const fstat_wu* wu, WuDev& v, Tile& t, hipStream_t s
   if (!width) return FSTAT_OK;
   // the split with the costs of paired tiles; pairs serve its ranges of at most 8
   const Tile tp = complete_tile(p, wu, t, true);
+  if (default_tile_used && !wave_beats_tile(p, wu, true) && grid_slots(wu, tp, np) > grid_slots(wu, t, 0))
+    return FSTAT_OK;
   bool small = std::all_of(tp.fd_split, tp.fd_split + fstat::kSplitSizes, [](int32_t x) { return x == 0; });
   for (int i = 0; i < fstat::kSplitSizes; ++i) small = small || (fstat::split_nfd(i) <= 8 && tp.fd_split[i] > 0);
   if (!small) return FSTAT_OK;
@@ -1245,6 +1281,9 @@ int batch_unit_shapes(fstat_plan* p, const fstat_wu* wus, const std::vector<int>
     if (wus[k].n_sky < 4) continue;
     us[q].pair_width =
         make_pairs(&wus[k], p->bstat_h[k], p->sky_h + 3 * sky_off[k], p->pairs_h + sky_off[k], &us[q].n_pairs);
+    if (us[q].pair_width &&
+        !pairs_pay(us[q].n_pairs, wus[k].n_sky, slots_share(&wus[k], status_tau(p->bstat_h[k]))))
+      us[q].pair_width = 0;
     if (!us[q].pair_width) continue;
     const hipError_t e = hipMemcpyAsync(p->pairs_d + sky_off[k], p->pairs_h + sky_off[k],
                                         (size_t)us[q].n_pairs * sizeof(int2), hipMemcpyHostToDevice, st);
