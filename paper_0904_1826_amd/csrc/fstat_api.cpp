@@ -1183,22 +1183,23 @@ int prepare_pairs(fstat_plan* p, const fstat_wu* wu, WuDev& v, Tile& t, hipStrea
 //   coefficients, whose loads are half as wide): 0.24 us at 5e4 templates,
 //   1.04 at 4e5, 1.98 at 8.6e5 (4.5e11 pairs/s, the rate of its 64-byte loads);
 // - the tile kernels, however few their tiles, take the latency of a staged
-//   slice, a barrier and a thread's spindowns per SFT and launch: 1.10 us with
-//   4 per thread, 1.25 with 5, 1.28 with 6 or 7, 1.40 with 8, 2.08 with 16,
-//   summed over the ranges of a split, whose launches follow each other; they
-//   come down to 1.05e-6 us per template.
-// So 8 spindowns cross at 5.9e5 templates (1.43 against 1.04 us at 4.3e5, 1.60
-// against 1.68 at 7.2e5), 16 at 9.0e5 (2.10 against 1.98 at 8.6e5) and 24 =
-// 16 + 8 at 1.5e6 (3.40 against 2.76 us at 1.2e6, 3.39 against 3.52 at 1.55e6);
-// 8 with FP16 coefficients at 1.0e6.  One or two spindowns have no
+//   slice, a barrier and a thread's spindowns per SFT and launch: 0.98 us with
+//   4 per thread, 1.10 with 5, 1.12 with 6, 1.15 with 7, 1.34 with 8, 1.87
+//   with 16, summed over the ranges of a split, whose launches follow each
+//   other; they come down to 0.9e-6 us per template.
+// So 8 spindowns cross at 5.6e5 templates (1.27 against 1.03 us at 4.3e5, 1.40
+// against 1.68 at 7.2e5), 16 at 8.0e5 (1.94 against 1.32 us at 5.7e5, 1.89
+// against 1.98 at 8.6e5) and 24 = 16 + 8 at 1.4e6 (3.04 against 2.72 us at
+// 1.2e6, 3.05 against 3.52 at 1.55e6); 8 with FP16 coefficients at 9.8e5 (1.40
+// against 1.18 us at 8.6e5).  One or two spindowns have no
 // efficient tile (4.1 against 2.2 us at 8e5 templates x 1 spindown, 7.1 against
 // 6.7 at 2.9e6 x 2).  Units whose block of 16 spindowns outgrows the slice keep
 // the tiles: their spindowns share few cache lines.
 bool wave_beats_tile(const fstat_plan* p, const fstat_wu* wu, bool paired) {
   if (resolved_kernel(p) != fstat::KERNEL_INTERP || p->force_seg > 0) return false;
   if (wu->n_fd <= 2) return true;
-  static const double kFloor[17] = {0.0,  0.0, 0.0, 0.0, 1.10, 1.25, 1.28, 1.28, 1.40,
-                                    0.0, 0.0, 0.0, 0.0, 0.0,  0.0,  0.0,  2.08};
+  static const double kFloor[17] = {0.0,  0.0, 0.0, 0.0, 0.98, 1.10, 1.12, 1.15, 1.34,
+                                    0.0, 0.0, 0.0, 0.0, 0.0,  0.0,  0.0,  1.87};
   const FdSplit sp = split_spindowns(wu->n_fd, coef16(p) ? (1u << 8) | (1u << 4) : kAllSplitSizes, paired);
   double tile_us = 0.0;
   for (int i = 0; i < fstat::kSplitSizes; ++i)
