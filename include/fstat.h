@@ -372,6 +372,19 @@ int32_t fstat_sky_pairs(int64_t n_sky, const double* sky, double f0, double df, 
  * NULL `out`. */
 int fstat_spindown_split(int64_t n_fd, int32_t coef16, int32_t allow16, int32_t paired, int64_t* out);
 
+/* The form in which the interp kernels evaluate the slots (sky point, spindown)
+ * of a tile in one launch over tiles of the n units wus[0, n), of which unit k
+ * has max |tau| max_abs_tau[k] over its (sky, SFT) pairs and n_tiles[k] tiles
+ * (read: df, dfdot, t_sft, k_first, n_bins): 0: every slot loads its
+ * coefficients; 1: a slot keeps those of the slot before it where no lane of
+ * the wave moved to another bin, chosen if most of the tiles gain from it
+ * (frequencies and spindowns that move by about a bin or less) and it can
+ * evaluate every one of the units.  The results do not depend on the form (FP32
+ * coefficients, slices that hold every window; other tiles have one form).
+ * A host function: no device, plan or allocation involved.  Returns
+ * FSTAT_E_ARG for NULL arrays or n < 1. */
+int32_t fstat_slot_form(int32_t n, const fstat_wu* wus, const double* max_abs_tau, const int64_t* n_tiles);
+
 /* Duration in milliseconds of the last demodulation kernel of the last
  * fstat_compute / fstat_batch_compute call (after fstat_semicoherent: the
  * sum over its segments' demodulation kernels), measured with HIP events on

@@ -46,7 +46,7 @@ PHASES = {"fp64": FSTAT_PHASE_FP64, "split": FSTAT_PHASE_SPLIT_FP32}
 EXPORTS = ("fstat_plan_create", "fstat_compute", "fstat_batch_compute", "fstat_bins", "fstat_autotune",
            "fstat_last_kernel_ms", "fstat_plan_destroy", "fstat_strerror", "fstat_last_error",
            "fstat_detector_inputs", "fstat_semicoherent", "fstat_compute_noalloc", "fstat_interp_slice",
-           "fstat_last_tile", "fstat_spindown_split", "fstat_sky_pairs")
+           "fstat_last_tile", "fstat_spindown_split", "fstat_sky_pairs", "fstat_slot_form")
 LAST_TILE_LEN = 13                    # FSTAT_LAST_TILE_LEN
 NOALLOC_SCRATCH_BYTES = 128 << 20     # FSTAT_NOALLOC_SCRATCH_BYTES
 
@@ -135,6 +135,8 @@ def load_library(path: str = LIB_PATH):
     lib.fstat_sky_pairs.argtypes = [I64, ctypes.POINTER(D), D, D, I64, D, D, I64, D, D, D, D, D,
                                     ctypes.POINTER(I32), ctypes.POINTER(I64)]
     lib.fstat_sky_pairs.restype = I32
+    lib.fstat_slot_form.argtypes = [I32, ctypes.POINTER(fstat_wu), ctypes.POINTER(D), ctypes.POINTER(I64)]
+    lib.fstat_slot_form.restype = I32
     lib.fstat_plan_destroy.argtypes = [P]
     lib.fstat_plan_destroy.restype = None
     lib.fstat_strerror.argtypes = [ctypes.c_int]
@@ -478,6 +480,21 @@ def fstat_spindown_split(n_fd: int, coef16: bool = False, allow16: bool = True, 
     if rc != 0:
         raise FstatError(rc, f"fstat_spindown_split({n_fd}): {fstat_strerror(rc)}")
     return {b: int(n) for b, n in zip(SPLIT_SIZES, buf) if n}
+
+
+def fstat_slot_form(units) -> int:
+    """The form of a launch over tiles of several units (see include/fstat.h);
+    units: (df, dfdot, t_sft, k_first, n_bins, max_abs_tau, n_tiles) each."""
+    wus, taus, tiles = (t * len(units) for t in (fstat_wu, ctypes.c_double, ctypes.c_int64))
+    wus, taus, tiles = wus(), taus(), tiles()
+    for k, (df, dfdot, t_sft, k_first, n_bins, tau, n_tiles) in enumerate(units):
+        w = wus[k]
+        w.df, w.dfdot, w.t_sft, w.k_first, w.n_bins = df, dfdot, t_sft, k_first, n_bins
+        taus[k], tiles[k] = tau, n_tiles
+    rc = int(load_library().fstat_slot_form(len(units), wus, taus, tiles))
+    if rc < 0:
+        raise FstatError(rc, f"fstat_slot_form: {fstat_strerror(rc)}")
+    return rc
 
 
 def fstat_sky_pairs(sky, f0, df, n_f, fdot0, dfdot, n_fd, t_sft, max_abs_tau, max_p, max_v, max_r):

@@ -521,9 +521,26 @@ int interp_seg_tau(const fstat_wu* w, int nfd, int threads, bool c16, double max
 // form costs 3 %.
 bool slots_share(const fstat_wu* w, double max_abs_tau) {
   const double step = w->df * w->t_sft, shift = fabs(w->dfdot) * max_abs_tau * w->t_sft;
-  return 64.0 * (fabs(step - nearbyint(step)) + 1.1e-4 * fabs(step)) <= 0.25 && shift <= 1.0 &&
-         w->n_bins < (1 << 20);          // the form reads columns from the position's high word
+  return 64.0 * (fabs(step - nearbyint(step)) + 1.1e-4 * fabs(step)) <= 0.25 && shift <= 1.0;
 }
+
+// Whether the sharing form can evaluate the unit at all: it reads columns from
+// the position's high word, which holds them for a band below 2^20 bins.
+bool words_hold(const fstat_wu* w) { return w->n_bins < (1 << 20); }
+
+// The form of one launch over the tiles of one or more units whose slices hold
+// every window: the sharing one if most of its tiles are of units that gain
+// from it, and every unit is one that it can evaluate.
+struct SlotForm {
+  int64_t tiles = 0, shared = 0;
+  bool words = true;
+  void add(const fstat_wu* w, double max_abs_tau, int64_t n_tiles) {
+    tiles += n_tiles;
+    if (slots_share(w, max_abs_tau)) shared += n_tiles;
+    words = words && words_hold(w);
+  }
+  fstat::Path path() const { return words && 2 * shared > tiles ? fstat::kPathShared : fstat::kPathFast; }
+};
 
 int interp_seg(const fstat_plan* p, const fstat_wu* w, int nfd, int threads, bool* fits) {
   return interp_seg_tau(w, nfd, threads, coef16(p), p->max_abs_tau, p->max_p, fits);
@@ -661,7 +678,11 @@ Tile complete_tile(const fstat_plan* p, const fstat_wu* w, Tile t, bool paired =
         t.fast = t.fast && f;
       }
     }
-    if (t.fast && !coef16(p) && slots_share(w, p->max_abs_tau)) t.fast = fstat::kPathShared;
+    if (t.fast && !coef16(p)) {
+      SlotForm form;
+      form.add(w, p->max_abs_tau, 1);
+      t.fast = form.path();
+    }
     if (p->force_seg > 0) {          // fault injection: a slice narrower than the windows need
       t.seg = p->force_seg;
       for (int i = 0; i < fstat::kSplitSizes; ++i) t.seg_split[i] = t.fd_split[i] > 0 ? p->force_seg : 0;
@@ -1328,7 +1349,7 @@ int batch_tables(const fstat_plan* p, const fstat_wu* wus, const std::vector<int
     const int i = c % NS, nsky = 1 + c / NS, nfd = fstat::split_nfd(i);
     tb->off[c] = ne;
     bool fast = true;
-    int64_t shared = 0;                // tiles of units whose slots share coefficients
+    SlotForm form;                     // one form for the whole launch
     for (int q = 0; q < m; ++q) {
       const int k = order[q];
       const bool paired = us[q].pair_width > 0 && nfd <= 8;
@@ -1360,11 +1381,10 @@ int batch_tables(const fstat_plan* p, const fstat_wu* wus, const std::vector<int
       e.n_tiles = fstat::interp_tiles(e.w, nfd, lo, hi, nsky);
       e.tile_begin = tb->tiles[c];
       tb->tiles[c] += e.n_tiles;
-      if (!coef16(p) && p->force_seg <= 0 && slots_share(&wus[k], status_tau(p->bstat_h[k]))) shared += e.n_tiles;
+      form.add(&wus[k], status_tau(p->bstat_h[k]), e.n_tiles);
       ++tb->mc[c];
     }
-    // one form for the whole launch: that of most of its tiles
-    tb->path[c] = !fast ? fstat::kPathSafe : 2 * shared > tb->tiles[c] ? fstat::kPathShared : fstat::kPathFast;
+    tb->path[c] = !fast ? fstat::kPathSafe : coef16(p) || p->force_seg > 0 ? fstat::kPathFast : form.path();
     for (int q = tb->off[c]; q < tb->off[c] + tb->mc[c]; ++q) eh[q].fast = tb->path[c];
   }
   return ne;
@@ -2292,6 +2312,13 @@ int32_t fstat_sky_pairs(int64_t n_sky, const double* sky, double f0, double df, 
   const int width = make_pairs(&w, g, sky, reinterpret_cast<int2*>(pairs), &np);
   *n_pairs = width ? np : 0;
   return width;
+}
+
+int32_t fstat_slot_form(int32_t n, const fstat_wu* wus, const double* max_abs_tau, const int64_t* n_tiles) {
+  if (n < 1 || !wus || !max_abs_tau || !n_tiles) return FSTAT_E_ARG;
+  SlotForm form;
+  for (int32_t k = 0; k < n; ++k) form.add(&wus[k], max_abs_tau[k], n_tiles[k]);
+  return form.path() - fstat::kPathFast;
 }
 
 int fstat_spindown_split(int64_t n_fd, int32_t coef16, int32_t allow16, int32_t paired, int64_t* out) {
