@@ -378,11 +378,12 @@ int fstat_spindown_split(int64_t n_fd, int32_t coef16, int32_t allow16, int32_t 
  * (read: df, dfdot, t_sft, k_first, n_bins): 0: every slot loads its
  * coefficients; 1: a slot keeps those of the slot before it where no lane of
  * the wave moved to another bin, chosen if most of the tiles gain from it
- * (frequencies and spindowns that move by about a bin or less) and it can
- * evaluate every one of the units.  The results do not depend on the form (FP32
- * coefficients, slices that hold every window; other tiles have one form).
- * A host function: no device, plan or allocation involved.  Returns
- * FSTAT_E_ARG for NULL arrays or n < 1. */
+ * (frequencies and spindowns that move by about a bin or less); 2: as 1, with
+ * k* and kappa read from the words of Dphi instead of converted, if every
+ * unit's band lies within [2^20, 2^21), where the words hold them exactly.
+ * The results do not depend on the form (FP32 coefficients, slices that hold
+ * every window; other tiles have one form).  A host function: no device, plan
+ * or allocation involved.  Returns FSTAT_E_ARG for NULL arrays or n < 1. */
 int32_t fstat_slot_form(int32_t n, const fstat_wu* wus, const double* max_abs_tau, const int64_t* n_tiles);
 
 /* Duration in milliseconds of the last demodulation kernel of the last

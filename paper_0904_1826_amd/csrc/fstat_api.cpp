@@ -104,10 +104,9 @@ struct fstat_plan {
   // stream and events of the batched graph's second chain (batch_chains)
   hipStream_t cap_side = nullptr;
   hipEvent_t cap_fork = nullptr, cap_join = nullptr;
-  // persistent grids of the batch kernels with split_nfd(c % kSplitSizes)
-  // spindowns and 1 + c / kSplitSizes sky points per tile, with [c][1] and
-  // without [c][0] the global-memory fallback
-  int batch_grid[2 * fstat::kSplitSizes][3] = {};
+  // persistent grids [c][path] of the batch kernels with split_nfd(c % kSplitSizes)
+  // spindowns and 1 + c / kSplitSizes sky points per tile
+  int batch_grid[2 * fstat::kSplitSizes][fstat::kPaths] = {};
   std::map<std::vector<int64_t>, hipGraphExec_t> graphs;
   // fault injection (host-side forcing of error paths); force_seg > 0 runs the
   // interp kernels without the global-memory path at that slice width
@@ -524,13 +523,17 @@ bool slots_share(const fstat_wu* w, double max_abs_tau) {
   return 64.0 * (fabs(step - nearbyint(step)) + 1.1e-4 * fabs(step)) <= 0.25 && shift <= 1.0;
 }
 
-// Whether the sharing form can evaluate the unit at all: it reads columns from
-// the position's high word, which holds them for a band below 2^20 bins.
-bool words_hold(const fstat_wu* w) { return w->n_bins < (1 << 20); }
+// Whether the words of every D-hat-phi of the unit (the band check keeps them
+// in the band) hold k* and kappa: the band lies within [2^20, 2^21).  At
+// 2000 sky points x 8 spindowns x 3600 frequencies x 2000 SFTs reading them
+// takes 102.3 ms, converting 106.5.
+bool words_hold(const fstat_wu* w) {
+  return w->k_first >= (1 << 20) && w->k_first + w->n_bins <= (1 << 21);
+}
 
 // The form of one launch over the tiles of one or more units whose slices hold
 // every window: the sharing one if most of its tiles are of units that gain
-// from it, and every unit is one that it can evaluate.
+// from it, reading words if every unit's hold.
 struct SlotForm {
   int64_t tiles = 0, shared = 0;
   bool words = true;
@@ -539,7 +542,9 @@ struct SlotForm {
     if (slots_share(w, max_abs_tau)) shared += n_tiles;
     words = words && words_hold(w);
   }
-  fstat::Path path() const { return words && 2 * shared > tiles ? fstat::kPathShared : fstat::kPathFast; }
+  fstat::Path path() const {
+    return 2 * shared <= tiles ? fstat::kPathFast : words ? fstat::kPathWords : fstat::kPathShared;
+  }
 };
 
 int interp_seg(const fstat_plan* p, const fstat_wu* w, int nfd, int threads, bool* fits) {
@@ -1137,7 +1142,7 @@ double grid_slots(const fstat_wu* wu, const Tile& t, int64_t np) {
     const int64_t round = 256 * (pair ? (nfd == 4 ? 4 : 3) : nfd == 16 ? 3 : 4);
     const int64_t groups = n_ft * ((n + nfd - 1) / nfd) * (pair ? np : wu->n_sky);
     const double tail = groups % round ? 0.2 + 0.8 * (double)((groups % round + 255) / 256 * 256) / (double)round : 0.0;
-    sum += ((double)(groups / round) + tail) * (double)round * nfd * (pair ? pair_cost(t.fast == fstat::kPathShared) : 1.0);
+    sum += ((double)(groups / round) + tail) * (double)round * nfd * (pair ? pair_cost(t.fast >= fstat::kPathShared) : 1.0);
   }
   return sum;
 }
@@ -1474,7 +1479,7 @@ int batch_interp(fstat_plan* p, const fstat_wu* wus, int n, const fstat_out* out
   for (int c = 0; c < NC; ++c) {
     const int nfd = fstat::split_nfd(c % NS), nsky = 1 + c / NS;
     if (!((sizes >> nfd) & 1u) || (nsky == 2 && (!pairing || nfd > 8)) || p->batch_grid[c][0]) continue;
-    for (int path = 0; path < 3; ++path) p->batch_grid[c][path] = fstat::interp_batch_grid(coef16(p), nfd, path, nsky);
+    for (int path = 0; path < fstat::kPaths; ++path) p->batch_grid[c][path] = fstat::interp_batch_grid(coef16(p), nfd, path, nsky);
   }
   // sky vectors and pair tables, at each unit's offset in the batch
   std::vector<int64_t> sky_off(n + 1, 0);

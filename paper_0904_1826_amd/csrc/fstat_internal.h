@@ -61,9 +61,11 @@ constexpr int kSplitSizes = 6;
 __host__ __device__ constexpr int split_nfd(int i) { return i == 0 ? 16 : 9 - i; }
 
 // Forms of an interp tile: with the global-memory path for SFTs whose windows
-// leave the slice, without it, and without it with the coefficients of a slot
-// kept for the next (slots_shared).
-enum Path : int32_t { kPathSafe = 0, kPathFast = 1, kPathShared = 2 };
+// leave the slice, without it, without it with the coefficients of a slot
+// kept for the next (slots_shared), and the last with k* and kappa read from
+// the words of D-hat-phi (bands within [2^20, 2^21) only).
+enum Path : int32_t { kPathSafe = 0, kPathFast = 1, kPathShared = 2, kPathWords = 3 };
+constexpr int kPaths = 4;
 
 // Tile shape of the demodulation kernels.
 struct Tile {
@@ -72,7 +74,7 @@ struct Tile {
   int32_t seg;      // interp: LDS segment width in bins (0: derived)
   int32_t sblock;   // interp: SFTs per launch (the SFT loop is split into launches of this many SFTs)
   int32_t threads;  // interp: work-group size, 64 or 256
-  int32_t fast;     // interp: Path; kPathFast or kPathShared if the slice holds every window of every SFT (no slice
+  int32_t fast;     // interp: Path; not kPathSafe if the slice holds every window of every SFT (no slice
                     // width was capped), so the kernel without the global-memory fallback may run
   int32_t pair_seg; // interp: > 0: the ranges of at most 8 spindowns per thread run tiles of two sky points
                     // (WuDev::sky_pairs) with this slice width

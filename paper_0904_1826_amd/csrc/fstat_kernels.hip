@@ -41,19 +41,11 @@ __device__ __forceinline__ double bin_scale(double tdot, double t_sft) { return 
 __device__ __forceinline__ double bin_offset(double fd, double tau, double p) { return (fd * tau) * p; }
 __device__ __forceinline__ double bin_position(double f, double q, double p) { return __builtin_fma(f, p, q); }
 
-// The interp kernels form D-hat-phi from the column kPosBias before the band's
-// first, that is with q + (kPosBias - k_first) in place of q: for a band below
-// 2^20 bins it then lies in [2^20, 2^21), where FP64 has 32 bits of fraction,
-// and is at hand as integers: the low word is kappa 2^32, the high word
-// kPosWord + column.  (Rounding: 2^-33 bins twice, against 2^-25 of kappa as
-// FP32.)  slots_shared reads the words, two instructions per pair instead of
-// four conversions and shifts (2000 sky points x 8 spindowns x 3600 frequencies
-// x 2000 SFTs: 106.5 -> 102.3 ms); the other forms convert the same value.
-constexpr int kPosBias = 1 << 20;
-constexpr uint32_t kPosWord = 0x41300000u;         // high word of 2^20
-__device__ __forceinline__ double column_offset(const WuDev& w, double fd, double tau, double p) {
-  return bin_offset(fd, tau, p) + (double)(kPosBias - w.k_first);
-}
+// In a band within [2^20, 2^21) FP64 has 32 bits of fraction, and D-hat-phi is
+// at hand as integers: its low word is kappa 2^32, its high word kPosWord + k*,
+// both exactly what the conversions give.  There slots_shared reads the words
+// (kPathWords), two instructions per pair instead of four conversions and shifts.
+constexpr uint32_t kPosWord = 0x41200000u;         // high word of 2^20, less 2^20
 
 __device__ __forceinline__ double fract64(double x) { return __builtin_amdgcn_fract(x); }
 
@@ -775,7 +767,7 @@ __device__ __forceinline__ void group_meta(const WuDev& w, const double2* const*
     const double2 g = geo[u][al0 + c];
     const int64_t i = (i0 + r < w.n_fd) ? i0 + r : w.n_fd - 1;
     const double fd = template_fd(w, i);
-    m.g[c][u][r] = column_offset(w, fd, g.x, g.y);
+    m.g[c][u][r] = bin_offset(fd, g.x, g.y);
     const double h = (0.5 * fd) * g.x;                 // (fdot / 2) tau
     const float q = w.phase_mode ? frac_split_product(split64(g.x), split64(h)) : (float)fract64(g.x * h);
     m.e[c][u][r] = make_float2(cos_rev(q), -sin_rev(q));
@@ -786,17 +778,16 @@ __device__ __forceinline__ void group_meta(const WuDev& w, const double2* const*
 #pragma unroll
     for (int u = 0; u < NSKY; ++u) {
       const double2 g = geo[u][al0 + t2];
-      const double ga = column_offset(w, template_fd(w, i0), g.x, g.y);
-      const double gb = column_offset(w, template_fd(w, i_last), g.x, g.y);
+      const double ga = bin_offset(template_fd(w, i0), g.x, g.y), gb = bin_offset(template_fd(w, i_last), g.x, g.y);
       const double d1 = bin_position(f_first, ga, g.y), d2 = bin_position(f_first, gb, g.y);
       const double d3 = bin_position(f_last, ga, g.y), d4 = bin_position(f_last, gb, g.y);
       const double mn = d1 < d2 ? d1 : d2, mx = d3 > d4 ? d3 : d4;
       lo_d = (u == 0 || mn < lo_d) ? mn : lo_d;
       hi_d = (u == 0 || mx > hi_d) ? mx : hi_d;
     }
-    // columns of the extreme bins; the band is below 2^31 bins
-    const int kmin = (int)(floor(lo_d) - (double)kPosBias);
-    const int kmax = (int)(floor(hi_d) - (double)kPosBias);
+    // column offsets of the extreme bins; the band is below 2^31 bins
+    const int kmin = (int)(floor(lo_d) - (double)w.k_first);
+    const int kmax = (int)(floor(hi_d) - (double)w.k_first);
     const int nb = (int)w.n_bins;
     const int max_lo = nb > W ? nb - W : 0;
     int lo = (kmin > 1 ? kmin : 1) - 1;           // one bin of slack
@@ -978,7 +969,7 @@ __device__ __forceinline__ void lgkm_wait() { __builtin_amdgcn_s_waitcnt(0xC07F)
 // x 3600 frequencies x 2000 SFTs 114.3, 109.1 ms (61 % of the loads left
 // out); 40 x 32 x 14400 x 2200 in batches 99.2, 90.3 ms; 301 x 8 x 2701 x 801
 // 6.59, 6.00 ms.
-template <int NFD, int NSKY, bool C16>
+template <int NFD, int NSKY, bool C16, bool WORDS>
 __device__ __forceinline__ void slots_shared(const double (&mg)[NSKY][NFD], const float2 (&me)[NSKY][NFD],
                                              const float4* seg, uint32_t boff, int Wp, double f, const double* pu,
                                              const float* cf, const float* sf, const float* au, const float* bu,
@@ -999,10 +990,16 @@ __device__ __forceinline__ void slots_shared(const double (&mg)[NSKY][NFD], cons
   };
   auto fetch = [&](int t) __attribute__((always_inline)) {
     const double dphi = bin_position(f, g[t % 3], pu[slot(t) / NFD]);
-    const u2v bits = __builtin_bit_cast(u2v, dphi);
-    uint32_t word = bits[1];
-    __asm__ volatile("" : "+v"(word));             // a 32-bit value (else: moved and compared as 64 bits)
-    kap[t & 1] = (float)bits[0] * 0x1p-32f;
+    uint32_t word;
+    if constexpr (WORDS) {
+      const u2v bits = __builtin_bit_cast(u2v, dphi);
+      word = bits[1];
+      __asm__ volatile("" : "+v"(word));           // a 32-bit value (else: moved and compared as 64 bits)
+      kap[t & 1] = (float)bits[0] * 0x1p-32f;
+    } else {
+      word = (uint32_t)(int)dphi;
+      kap[t & 1] = (float)fract64(dphi);
+    }
     if (t < 2 || __builtin_amdgcn_ballot_w64(word != at[t & 1])) {
       const LdsPtr q = lds_at(seg, (word << 4) + boff);
 #pragma unroll
@@ -1063,7 +1060,7 @@ template <int NFD, int S, int G, int NT, bool C16, int PATH, int NSKY = 1>
 __device__ __forceinline__ void interp_tile(const WuDev& w, int W, int64_t tile, int64_t al_begin, int64_t al_end,
                                             float4* cbuf0, float4* cbuf1, GroupMeta<NFD, S, NSKY>* meta, int64_t fd0,
                                             int64_t fd1) {
-  constexpr bool SAFE = PATH == kPathSafe, SHARE = PATH == kPathShared;
+  constexpr bool SAFE = PATH == kPathSafe, SHARE = PATH >= kPathShared, WORDS = PATH == kPathWords;
   const int tid = threadIdx.x;
   const int64_t n_fdb = (fd1 - fd0 + NFD - 1) / NFD;
   using F = SliceForm<NT, C16>;
@@ -1103,6 +1100,7 @@ __device__ __forceinline__ void interp_tile(const WuDev& w, int W, int64_t tile,
     brow[u] = w.b + su[u] * w.n_sft;
   }
   const int n = (int)(al_end - al_begin);
+  const int k_first = (int)w.k_first;
 
   // accumulators of (sky point u, spindown r) at slot u NFD + r
   constexpr int NSL = NSKY * NFD;
@@ -1166,9 +1164,8 @@ __device__ __forceinline__ void interp_tile(const WuDev& w, int W, int64_t tile,
       cf[u] = cos_rev(pf);
       sf[u] = sin_rev(pf);
     }
-    // byte offset in row 0 of the slice of the bin at position k (column
-    // k - kPosBias; with SHARE its high word): 16 k - 16 (bias + lo), in 32-bit
-    // modular arithmetic
+    // byte offset in row 0 of the slice of bin k, from k (WORDS: kPosWord + k):
+    // 16 k - 16 (k_first + lo), in 32-bit modular arithmetic
     // (uniform; kept opaque in a scalar register so that the compiler forms one
     // shift-and-add per pair rather than folding the sign into a subtraction).
     // The reads go through a pointer to the buffer itself, not an address made
@@ -1176,7 +1173,7 @@ __device__ __forceinline__ void interp_tile(const WuDev& w, int W, int64_t tile,
     // write the other buffer, and not wait for them before the first read
     // (2000 sky points x 8 spindowns x 3600 frequencies x 2000 SFTs: 115.4 ->
     // 114.3 ms).
-    uint32_t boff = __builtin_amdgcn_readfirstlane(0u - 16u * ((SHARE ? kPosWord : (uint32_t)kPosBias) + (uint32_t)m.lo[kk]));
+    uint32_t boff = __builtin_amdgcn_readfirstlane(0u - 16u * ((WORDS ? kPosWord : 0u) + (uint32_t)(k_first + m.lo[kk])));
     __asm__ volatile("" : "+s"(boff));
     // SAFE: an SFT whose windows are not all in the slice reads its
     // coefficients from global memory.  Otherwise the host has shown that
@@ -1187,7 +1184,7 @@ __device__ __forceinline__ void interp_tile(const WuDev& w, int W, int64_t tile,
     // schedules across SFTs and spills.
     if (__builtin_amdgcn_readfirstlane(m.fast[kk])) {
       if constexpr (SHARE) {
-        slots_shared<NFD, NSKY, C16>(m.g[kk], m.e[kk], seg, boff, Wp, f, pu, cf, sf, au, bu, far, fai, fbr, fbi);
+        slots_shared<NFD, NSKY, C16, WORDS>(m.g[kk], m.e[kk], seg, boff, Wp, f, pu, cf, sf, au, bu, far, fai, fbr, fbi);
       } else {
 #pragma unroll
       for (int x = 0; x < NSL; ++x) {
@@ -1211,11 +1208,11 @@ __device__ __forceinline__ void interp_tile(const WuDev& w, int W, int64_t tile,
         const double dphi = bin_position(f, m.g[kk][u][r], pu[u]);
         const float kap = (float)fract64(dphi);
         if constexpr (C16) {
-          const CoefSet16 cs = load_coef16_global(w, al, (int64_t)(int)dphi - kPosBias);
+          const CoefSet16 cs = load_coef16_global(w, al, (int64_t)(int)dphi - w.k_first);
           interp_accumulate16(cs.c[0], cs.c[1], kap, cf[u], sf[u], m.e[kk][u][r], au[u], bu[u], far[x], fai[x],
                               fbr[x], fbi[x]);
         } else {
-          const CoefSet cs = load_coef_global(w, al, (int64_t)(int)dphi - kPosBias);
+          const CoefSet cs = load_coef_global(w, al, (int64_t)(int)dphi - w.k_first);
           interp_accumulate(cs.c[0], cs.c[1], cs.c[2], cs.c[3], kap, cf[u], sf[u], m.e[kk][u][r], au[u], bu[u],
                             far[x], fai[x], fbr[x], fbi[x]);
         }
@@ -1416,11 +1413,11 @@ struct WaveFetch {
     a = C16 ? arow[al] * sa : arow[al];
     b = C16 ? brow[al] * sa : brow[al];
   }
-  __device__ __forceinline__ WaveSft<SPLIT> value(const WuDev& w, double fd) const {
+  __device__ __forceinline__ WaveSft<SPLIT> value(double fd) const {
     WaveSft<SPLIT> x;
     x.tau = g.x;
     x.p = g.y;
-    x.q = column_offset(w, fd, g.x, g.y);
+    x.q = bin_offset(fd, g.x, g.y);
     const double h = (0.5 * fd) * g.x;
     float ph;
     if constexpr (SPLIT) {
@@ -1492,7 +1489,7 @@ __global__ __launch_bounds__(kThreads, 3) void demod_wave_kernel(WuDev w) {
   const double2* geo = w.geo + s * w.n_sft;
   const float* arow = w.a + s * w.n_sft;
   const float* brow = w.b + s * w.n_sft;
-  const int n = (int)w.n_sft, nb = (int)w.n_bins;
+  const int n = (int)w.n_sft, k_first = (int)w.k_first, nb = (int)w.n_bins;
   constexpr int ROWS = C16 ? kRows16 : kCoefPairs;
   typedef typename std::conditional<C16, CoefSet16, CoefSet>::type Set;
   WaveSft<SPLIT>* my = lds[wv];
@@ -1502,7 +1499,7 @@ __global__ __launch_bounds__(kThreads, 3) void demod_wave_kernel(WuDev w) {
     next.load(w, geo, arow, brow, al0 + lane < n ? al0 + lane : n - 1);
   };
   auto publish = [&](int al0) __attribute__((always_inline)) {
-    const WaveSft<SPLIT> x = next.value(w, fd);
+    const WaveSft<SPLIT> x = next.value(fd);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     my[(al0 + lane) & 127] = x;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1526,7 +1523,7 @@ __global__ __launch_bounds__(kThreads, 3) void demod_wave_kernel(WuDev w) {
       const uint64_t base = coef + (uint64_t)al * (uint64_t)(ROWS * row);
       const __amdgpu_buffer_rsrc_t rsrc =
           __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(base), (short)0, (int)(ROWS * row), 0x00020000);
-      const int off = (int)(16u * (uint32_t)((int)dphi - kPosBias));
+      const int off = (int)(16u * (uint32_t)((int)dphi - k_first));
 #pragma unroll
       for (int q = 0; q < ROWS; ++q) {
         const v4f v = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, (int)(q * row), 0));
@@ -1866,7 +1863,8 @@ static int batch_grid_t(int cus) {
 
 template <int NFD, int NSKY = 1>
 static int batch_grid_of(int path, int cus) {
-  return path == kPathShared ? batch_grid_t<NFD, false, kPathShared, NSKY>(cus)
+  return path == kPathWords ? batch_grid_t<NFD, false, kPathWords, NSKY>(cus)
+         : path == kPathShared ? batch_grid_t<NFD, false, kPathShared, NSKY>(cus)
          : path == kPathFast ? batch_grid_t<NFD, false, kPathFast, NSKY>(cus)
                              : batch_grid_t<NFD, false, kPathSafe, NSKY>(cus);
 }
@@ -1911,7 +1909,8 @@ hipError_t launch_interp_batch(const BatchEntry* ents_dev, int n_ent, int64_t to
                      chunk, al0, al1)
 #define FSTAT_BATCH_LAUNCH2(N, K) \
   do { \
-    if (path == kPathShared) FSTAT_BATCH_LAUNCH(N, false, kPathShared, K); \
+    if (path == kPathWords) FSTAT_BATCH_LAUNCH(N, false, kPathWords, K); \
+    else if (path == kPathShared) FSTAT_BATCH_LAUNCH(N, false, kPathShared, K); \
     else if (path == kPathFast) FSTAT_BATCH_LAUNCH(N, false, kPathFast, K); \
     else FSTAT_BATCH_LAUNCH(N, false, kPathSafe, K); \
   } while (0)
@@ -1972,11 +1971,14 @@ static hipError_t launch_interp_t(const WuDev& w, const Tile& t, hipStream_t st,
   return hipSuccess;
 }
 
-// The fast form of an FP32 tile, with or without shared coefficients.
+// The fast forms of an FP32 tile.
 template <int NFD, int S, int MINW, int G, int NSKY = 1>
 static hipError_t launch_fast_t(const WuDev& w, const Tile& t, hipStream_t st, int64_t fd0, int64_t fd1) {
-  return t.fast == kPathShared ? launch_interp_t<NFD, S, MINW, G, kThreads, false, kPathShared, NSKY>(w, t, st, fd0, fd1)
-                               : launch_interp_t<NFD, S, MINW, G, kThreads, false, kPathFast, NSKY>(w, t, st, fd0, fd1);
+  switch (t.fast) {
+    case kPathWords: return launch_interp_t<NFD, S, MINW, G, kThreads, false, kPathWords, NSKY>(w, t, st, fd0, fd1);
+    case kPathShared: return launch_interp_t<NFD, S, MINW, G, kThreads, false, kPathShared, NSKY>(w, t, st, fd0, fd1);
+    default: return launch_interp_t<NFD, S, MINW, G, kThreads, false, kPathFast, NSKY>(w, t, st, fd0, fd1);
+  }
 }
 
 int interp_max_seg(int threads, bool c16) {
