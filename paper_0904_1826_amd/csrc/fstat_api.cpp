@@ -182,7 +182,8 @@ int check_launch(fstat_plan* p, hipError_t e, const char* what) {
 // The previous call's tiles that met an SFT outside their slice, once the copy has landed:
 // an error naming them (their templates' outputs are NaN), else FSTAT_OK.
 int check_prev_drops(fstat_plan* p, hipStream_t st) {
-  if (p->last_event && st != p->last_stream) (void)hipEventSynchronize(p->last_event);
+  // (the per-thread stream is another one in each thread)
+  if (p->last_event && (st != p->last_stream || st == hipStreamPerThread)) (void)hipEventSynchronize(p->last_event);
   if (!p->drop_pending) return FSTAT_OK;
   p->drop_pending = false;
   if (hipEventSynchronize(p->ev_drop) != hipSuccess) return set_err(p, FSTAT_E_DEVICE, "previous call did not complete");
@@ -216,6 +217,7 @@ void queue_drop_check(fstat_plan* p, fstat::GeoStatus* src_d, fstat::GeoStatus* 
   if (hipMemcpyAsync(dst_h, src_d, n * sizeof(fstat::GeoStatus), hipMemcpyDeviceToHost, st) != hipSuccess ||
       hipEventRecord(p->ev_drop, st) != hipSuccess) {
     (void)hipGetLastError();
+    (void)hipStreamSynchronize(st);          // nothing marks the call's end
     return;
   }
   p->drop_pending = true;
@@ -241,6 +243,17 @@ void end_call(fstat_plan* p, const Tile& t, int kernel, bool toplist, fstat::Geo
   p->last_event = p->ev1;
   if (kernel == fstat::KERNEL_INTERP && t.wave && !toplist) return;
   p->last_event = hipEventRecord(p->ev_drop, st) == hipSuccess ? p->ev_drop : nullptr;
+  if (!p->last_event) (void)hipStreamSynchronize(st);
+}
+
+// The end of a call that may have queued work before it failed (rc not
+// FSTAT_OK): coefficient passes and tables go ahead of the checks, so the call
+// waits for what it queued.  Else the next one, on another stream, would share
+// the plan's scratch and tables with it, or, for fstat_compute_noalloc, another
+// plan's call the static scratch.
+int settle(hipStream_t st, int rc) {
+  if (rc) (void)hipStreamSynchronize(st);
+  return rc;
 }
 
 bool finite(double x) { return std::isfinite(x); }
@@ -1705,6 +1718,166 @@ int batch_interp(fstat_plan* p, const fstat_wu* wus, int n, const fstat_out* out
   return FSTAT_OK;
 }
 
+// One validated unit, its scratch in place: check, coefficients, demodulation.
+// On the static scratch: no carried Fa, Fb, so one launch over all SFTs, and no
+// pairs, whose table is allocated.
+int run_unit(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, WuDev v, fstat::GeoStatus* status,
+             bool static_scratch, hipStream_t st) {
+  const int kernel = resolved_kernel(p);
+  const bool interp = kernel == fstat::KERNEL_INTERP, pair = !static_scratch && may_pair(p, wu);
+  int rc = queue_geometry(p, v, status, st, pair ? wu : nullptr, interp);
+  if (rc) return rc;
+  const bool ahead = wave_ahead(p, wu, out, pair);
+  if (ahead) {
+    rc = queue_wave_ahead(p, v, status, st);
+    if (rc) return rc;
+  }
+  rc = wait_geometry(p, -1);
+  if (rc) p->timed = false;
+  if (rc || (ahead && p->fits16)) return rc;
+  bool dflt = false;
+  Tile t = pick_tile(p, wu, &dflt);
+  if (static_scratch) t.sblock = 0;
+  else if ((rc = prepare_pairs(p, wu, v, t, st, dflt))) return rc;
+  pick_wave(p, wu, t, dflt);
+  if (may_drop(kernel, t)) rc = reset_drops(p, status, st);
+  if (rc == FSTAT_OK) rc = run_demod(p, v, t, st, interp);
+  if (rc == FSTAT_OK) end_call(p, t, kernel, out->top_k > 0, status, st);
+  return rc;
+}
+
+// Batched form of the direct kernel: one unit after the other.
+int batch_direct(fstat_plan* p, const fstat_wu* wus, int n, const fstat_out* outs, hipStream_t st) {
+  for (int k = 0; k < n; ++k) {
+    int rc = ensure_scratch(p, &wus[k]);
+    if (rc) return rc;
+    rc = ensure_toplist(p, &outs[k]);
+    if (rc) return rc;
+    WuDev v = make_dev(p, &wus[k], &outs[k]);
+    rc = run_geometry(p, v, st, k);
+    if (rc) return rc;
+    rc = run_demod(p, v, pick_tile(p, &wus[k]), st, false);
+    if (rc) return rc;
+  }
+  end_call(p, Tile{}, fstat::KERNEL_DIRECT, true, p->status_d, st);
+  return FSTAT_OK;
+}
+
+// The validated segments of a semi-coherent call.
+int run_segments(fstat_plan* p, const fstat_wu* segs, int n_seg, const fstat_out* out, hipStream_t st) {
+  const fstat_wu& g = segs[0];
+  int rc = ensure_toplist(p, out);
+  if (rc) return rc;
+  rc = reset_drops(p, p->status_d, st);
+  if (rc) return rc;
+  fstat_out o = *out;
+  o.top_k = 0;                       // the toplist is taken of the sum, after the last segment
+  // Every segment's geometry, A, B, C and band check first, with one wait for
+  // all of them (which also brings the sky vectors for the pairing), then the
+  // segments' coefficient passes and demodulations back to back on the
+  // stream: nothing is demodulated unless every segment passed its check,
+  // and the device does not wait for the host between segments.
+  const int64_t n = g.n_sky;
+  for (int k = 0; k < n_seg; ++k) {  // buffers reach their largest size before any pointer is taken
+    rc = ensure_scratch(p, &segs[k]);
+    if (rc) return rc;
+  }
+  std::vector<size_t> goff((size_t)n_seg + 1, 0);
+  for (int k = 0; k < n_seg; ++k)
+    goff[k + 1] = goff[k] + align256((size_t)n * segs[k].n_sft * sizeof(double2)) + align256((size_t)n * sizeof(double4));
+  rc = dev_alloc(p, &p->seg_arena, &p->seg_arena_bytes, goff[n_seg], "segment geometry");
+  if (rc) return rc;
+  rc = ensure_pinned_pair(p, &p->bstat_d, &p->bstat_h, &p->bstat_cap, (size_t)n_seg, "segment status");
+  if (rc) return rc;
+  const bool pair = may_pair(p, &g);
+  p->sky_staged = nullptr;
+  if (pair) {
+    const size_t need = (size_t)n_seg * 3 * (size_t)n;
+    if (p->sky_h_cap < need) {
+      if (p->sky_h) (void)hipHostFree(p->sky_h);
+      p->sky_h = nullptr;
+      p->sky_h_cap = 0;
+      if (hipHostMalloc((void**)&p->sky_h, need * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        return set_err(p, FSTAT_E_NOMEM, "sky vectors: allocation of %lld entries failed", (long long)(n * n_seg));
+      }
+      p->sky_h_cap = need;
+    }
+    rc = ensure_pinned_pair(p, &p->pairs_d, &p->pairs_h, &p->pairs_cap, (size_t)n_seg * (size_t)n, "sky pairs");
+    if (rc) return rc;
+  }
+  while (p->seg_ev.size() < 2 * (size_t)n_seg) {
+    hipEvent_t e = nullptr;
+    if (hipEventCreate(&e) != hipSuccess) return set_err(p, FSTAT_E_DEVICE, "semi-coherent: event creation failed");
+    p->seg_ev.push_back(e);
+  }
+  rc = check_launch(p, fstat::launch_fill_int((int*)p->bstat_d, 0,
+                                              n_seg * (int)(sizeof(fstat::GeoStatus) / sizeof(int)), st),
+                    "status reset");
+  if (rc) return rc;
+  std::vector<WuDev> vs((size_t)n_seg);
+  for (int k = 0; k < n_seg; ++k) {
+    WuDev v = make_dev(p, &segs[k], &o);
+    char* base = (char*)p->seg_arena + goff[k];
+    v.geo = (double2*)base;
+    v.abcd = (double4*)(base + align256((size_t)n * segs[k].n_sft * sizeof(double2)));
+    v.accumulate = k > 0;
+    const bool by_kernel = pair && n <= kSkyByKernel;
+    rc = check_launch(p, fstat::launch_geometry(v, p->bstat_d + k, p->bstat_h + k,
+                                                by_kernel ? p->sky_h + 3 * (size_t)n * k : nullptr, st, nullptr),
+                      "geometry kernel");
+    if (rc) return rc;
+    if (pair && !by_kernel) {
+      const hipError_t e = hipMemcpyAsync(p->sky_h + 3 * (size_t)n * k, segs[k].sky, (size_t)(3 * n) * sizeof(double),
+                                          hipMemcpyDeviceToHost, st);
+      if (e != hipSuccess) return hip_err(p, e, "sky vector copy");
+    }
+    vs[(size_t)k] = v;
+  }
+  // the first segment's coefficients depend on no check and write only scratch
+  hipError_t e = hipEventRecord(p->ev_geo, st);
+  const bool interp = resolved_kernel(p) == fstat::KERNEL_INTERP;
+  if (e == hipSuccess && interp) {
+    rc = run_coef(p, vs[0], st);
+    if (rc) return rc;
+  }
+  if (e == hipSuccess) e = hipEventSynchronize(p->ev_geo);
+  if (e != hipSuccess) return hip_err(p, e, "geometry kernel");
+  for (int k = 0; k < n_seg; ++k) {
+    const int bits = p->bstat_h[k].flags;
+    if (bits & 1) return set_err(p, FSTAT_E_BAND, "segment %d: a Dirichlet window [k*-D+1, k*+D] leaves the stored band", k);
+    if (bits & 2) return set_err(p, FSTAT_E_ARG, "segment %d: antenna-pattern matrix is singular (A B - C^2 <= 0)", k);
+  }
+  for (int k = 0; k < n_seg; ++k) {
+    WuDev v = vs[(size_t)k];
+    p->max_abs_tau = status_tau(p->bstat_h[k]);       // the slice widths of this segment's tile
+    p->max_p = status_p(p->bstat_h[k]);
+    p->fits16 = (p->bstat_h[k].flags & fstat::kGeoFits16) != 0;
+    bool dflt = false;
+    Tile t = pick_tile(p, &segs[k], &dflt);
+    t.pair_seg = 0;
+    if (pair && pairs_apply(p, &segs[k], t)) {
+      rc = pair_sky(p, &segs[k], v, t, st, dflt, p->bstat_h[k], p->sky_h + 3 * (size_t)n * k,
+                    p->pairs_h + (size_t)n * k, p->pairs_d + (size_t)n * k);
+      if (rc) return rc;
+    }
+    pick_wave(p, &segs[k], t, dflt);
+    rc = run_demod(p, v, t, st, interp && k == 0, p->seg_ev[2 * (size_t)k], p->seg_ev[2 * (size_t)k + 1]);
+    if (rc) return rc;
+  }
+  p->seg_timed = n_seg;
+  if (out->top_k > 0) {
+    WuDev v = make_dev(p, &g, out);
+    rc = check_launch(p, fstat::launch_fill_int((int*)v.cand_count, 0, 2, st), "toplist counter reset");
+    if (rc) return rc;
+    rc = check_launch(p, fstat::launch_cand_scan(v, st), "semi-coherent candidate scan");
+    if (rc) return rc;
+    rc = check_launch(p, fstat::launch_top_select(v, st), "toplist selection");
+  }
+  if (rc == FSTAT_OK) queue_drop_check(p, p->status_d, p->status_h, 0, st);
+  return rc;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1823,27 +1996,7 @@ int fstat_compute(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void*
   if (rc) return rc;
   rc = ensure_toplist(p, out);
   if (rc) return rc;
-  WuDev v = make_dev(p, wu, out);
-  const bool interp = resolved_kernel(p) == fstat::KERNEL_INTERP, pair = may_pair(p, wu);
-  rc = queue_geometry(p, v, p->status_d, st, pair ? wu : nullptr, interp);
-  if (rc) return rc;
-  const bool ahead = wave_ahead(p, wu, out, pair);
-  if (ahead) {
-    rc = queue_wave_ahead(p, v, p->status_d, st);
-    if (rc) return rc;
-  }
-  rc = wait_geometry(p, -1);
-  if (rc) p->timed = false;
-  if (rc || (ahead && p->fits16)) return rc;
-  bool dflt = false;
-  Tile t = pick_tile(p, wu, &dflt);
-  rc = prepare_pairs(p, wu, v, t, st, dflt);
-  if (rc) return rc;
-  pick_wave(p, wu, t, dflt);
-  if (may_drop(resolved_kernel(p), t)) rc = reset_drops(p, p->status_d, st);
-  if (rc == FSTAT_OK) rc = run_demod(p, v, t, st, interp);
-  if (rc == FSTAT_OK) end_call(p, t, resolved_kernel(p), out->top_k > 0, p->status_d, st);
-  return rc;
+  return settle(st, run_unit(p, wu, out, make_dev(p, wu, out), p->status_d, false, st));
 }
 
 int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void* stream) {
@@ -1892,24 +2045,7 @@ int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* ou
     v.cand = (uint4*)(base + fstat::kStaticCandOff);
     v.cand_count = (unsigned long long*)(base + fstat::kStaticCountOff);
   }
-  rc = queue_geometry(p, v, status, st, nullptr, interp);
-  if (rc) return rc;
-  const bool ahead = wave_ahead(p, wu, out, false);
-  if (ahead) {
-    rc = queue_wave_ahead(p, v, status, st);
-    if (rc) return rc;
-  }
-  rc = wait_geometry(p, -1);
-  if (rc) p->timed = false;
-  if (rc || (ahead && p->fits16)) return rc;
-  bool dflt = false;
-  Tile t = pick_tile(p, wu, &dflt);
-  t.sblock = 0;                      // one launch over all SFTs: no carried Fa, Fb
-  pick_wave(p, wu, t, dflt);
-  if (may_drop(resolved_kernel(p), t)) rc = reset_drops(p, status, st);
-  if (rc == FSTAT_OK) rc = run_demod(p, v, t, st, interp);
-  if (rc == FSTAT_OK) end_call(p, t, resolved_kernel(p), out->top_k > 0, status, st);
-  return rc;
+  return settle(st, run_unit(p, wu, out, v, status, true, st));
 }
 
 int fstat_batch_compute(fstat_plan* p, const fstat_wu* wus, int32_t n_wu, const fstat_out* outs, void* stream) {
@@ -1928,22 +2064,8 @@ int fstat_batch_compute(fstat_plan* p, const fstat_wu* wus, int32_t n_wu, const 
   if (hipSetDevice(p->device) != hipSuccess) return set_err(p, FSTAT_E_DEVICE, "hipSetDevice failed");
   hipStream_t st = (hipStream_t)stream;
   if (n_wu == 0) return FSTAT_OK;
-  if (resolved_kernel(p) == fstat::KERNEL_INTERP) return batch_interp(p, wus, n_wu, outs, st);
-  // direct kernel: one work unit after the other
-  int rc = FSTAT_OK;
-  for (int k = 0; k < n_wu; ++k) {
-    rc = ensure_scratch(p, &wus[k]);
-    if (rc) return rc;
-    rc = ensure_toplist(p, &outs[k]);
-    if (rc) return rc;
-    WuDev v = make_dev(p, &wus[k], &outs[k]);
-    rc = run_geometry(p, v, st, k);
-    if (rc) return rc;
-    rc = run_demod(p, v, pick_tile(p, &wus[k]), st, false);
-    if (rc) return rc;
-  }
-  end_call(p, Tile{}, fstat::KERNEL_DIRECT, true, p->status_d, st);
-  return FSTAT_OK;
+  return settle(st, resolved_kernel(p) == fstat::KERNEL_INTERP ? batch_interp(p, wus, n_wu, outs, st)
+                                                               : batch_direct(p, wus, n_wu, outs, st));
 }
 
 int fstat_semicoherent(fstat_plan* p, const fstat_wu* segs, int32_t n_seg, const fstat_out* out, void* stream) {
@@ -1968,116 +2090,7 @@ int fstat_semicoherent(fstat_plan* p, const fstat_wu* segs, int32_t n_seg, const
   }
   if (hipSetDevice(p->device) != hipSuccess) return set_err(p, FSTAT_E_DEVICE, "hipSetDevice failed");
   hipStream_t st = (hipStream_t)stream;
-  int rc = ensure_toplist(p, out);
-  if (rc) return rc;
-  rc = reset_drops(p, p->status_d, st);
-  if (rc) return rc;
-  fstat_out o = *out;
-  o.top_k = 0;                       // the toplist is taken of the sum, after the last segment
-  // Every segment's geometry, A, B, C and band check first, with one wait for
-  // all of them (which also brings the sky vectors for the pairing), then the
-  // segments' coefficient passes and demodulations back to back on the
-  // stream: nothing is demodulated unless every segment passed its check,
-  // and the device does not wait for the host between segments.
-  const int64_t n = g.n_sky;
-  for (int k = 0; k < n_seg; ++k) {  // buffers reach their largest size before any pointer is taken
-    rc = ensure_scratch(p, &segs[k]);
-    if (rc) return rc;
-  }
-  std::vector<size_t> goff((size_t)n_seg + 1, 0);
-  for (int k = 0; k < n_seg; ++k)
-    goff[k + 1] = goff[k] + align256((size_t)n * segs[k].n_sft * sizeof(double2)) + align256((size_t)n * sizeof(double4));
-  rc = dev_alloc(p, &p->seg_arena, &p->seg_arena_bytes, goff[n_seg], "segment geometry");
-  if (rc) return rc;
-  rc = ensure_pinned_pair(p, &p->bstat_d, &p->bstat_h, &p->bstat_cap, (size_t)n_seg, "segment status");
-  if (rc) return rc;
-  const bool pair = may_pair(p, &g);
-  p->sky_staged = nullptr;
-  if (pair) {
-    const size_t need = (size_t)n_seg * 3 * (size_t)n;
-    if (p->sky_h_cap < need) {
-      if (p->sky_h) (void)hipHostFree(p->sky_h);
-      p->sky_h = nullptr;
-      p->sky_h_cap = 0;
-      if (hipHostMalloc((void**)&p->sky_h, need * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        return set_err(p, FSTAT_E_NOMEM, "sky vectors: allocation of %lld entries failed", (long long)(n * n_seg));
-      }
-      p->sky_h_cap = need;
-    }
-    rc = ensure_pinned_pair(p, &p->pairs_d, &p->pairs_h, &p->pairs_cap, (size_t)n_seg * (size_t)n, "sky pairs");
-    if (rc) return rc;
-  }
-  while (p->seg_ev.size() < 2 * (size_t)n_seg) {
-    hipEvent_t e = nullptr;
-    if (hipEventCreate(&e) != hipSuccess) return set_err(p, FSTAT_E_DEVICE, "semi-coherent: event creation failed");
-    p->seg_ev.push_back(e);
-  }
-  rc = check_launch(p, fstat::launch_fill_int((int*)p->bstat_d, 0,
-                                              n_seg * (int)(sizeof(fstat::GeoStatus) / sizeof(int)), st),
-                    "status reset");
-  if (rc) return rc;
-  std::vector<WuDev> vs((size_t)n_seg);
-  for (int k = 0; k < n_seg; ++k) {
-    WuDev v = make_dev(p, &segs[k], &o);
-    char* base = (char*)p->seg_arena + goff[k];
-    v.geo = (double2*)base;
-    v.abcd = (double4*)(base + align256((size_t)n * segs[k].n_sft * sizeof(double2)));
-    v.accumulate = k > 0;
-    const bool by_kernel = pair && n <= kSkyByKernel;
-    rc = check_launch(p, fstat::launch_geometry(v, p->bstat_d + k, p->bstat_h + k,
-                                                by_kernel ? p->sky_h + 3 * (size_t)n * k : nullptr, st, nullptr),
-                      "geometry kernel");
-    if (rc) return rc;
-    if (pair && !by_kernel) {
-      const hipError_t e = hipMemcpyAsync(p->sky_h + 3 * (size_t)n * k, segs[k].sky, (size_t)(3 * n) * sizeof(double),
-                                          hipMemcpyDeviceToHost, st);
-      if (e != hipSuccess) return hip_err(p, e, "sky vector copy");
-    }
-    vs[(size_t)k] = v;
-  }
-  // the first segment's coefficients depend on no check and write only scratch
-  hipError_t e = hipEventRecord(p->ev_geo, st);
-  const bool interp = resolved_kernel(p) == fstat::KERNEL_INTERP;
-  if (e == hipSuccess && interp) {
-    rc = run_coef(p, vs[0], st);
-    if (rc) return rc;
-  }
-  if (e == hipSuccess) e = hipEventSynchronize(p->ev_geo);
-  if (e != hipSuccess) return hip_err(p, e, "geometry kernel");
-  for (int k = 0; k < n_seg; ++k) {
-    const int bits = p->bstat_h[k].flags;
-    if (bits & 1) return set_err(p, FSTAT_E_BAND, "segment %d: a Dirichlet window [k*-D+1, k*+D] leaves the stored band", k);
-    if (bits & 2) return set_err(p, FSTAT_E_ARG, "segment %d: antenna-pattern matrix is singular (A B - C^2 <= 0)", k);
-  }
-  for (int k = 0; k < n_seg; ++k) {
-    WuDev v = vs[(size_t)k];
-    p->max_abs_tau = status_tau(p->bstat_h[k]);       // the slice widths of this segment's tile
-    p->max_p = status_p(p->bstat_h[k]);
-    p->fits16 = (p->bstat_h[k].flags & fstat::kGeoFits16) != 0;
-    bool dflt = false;
-    Tile t = pick_tile(p, &segs[k], &dflt);
-    t.pair_seg = 0;
-    if (pair && pairs_apply(p, &segs[k], t)) {
-      rc = pair_sky(p, &segs[k], v, t, st, dflt, p->bstat_h[k], p->sky_h + 3 * (size_t)n * k,
-                    p->pairs_h + (size_t)n * k, p->pairs_d + (size_t)n * k);
-      if (rc) return rc;
-    }
-    pick_wave(p, &segs[k], t, dflt);
-    rc = run_demod(p, v, t, st, interp && k == 0, p->seg_ev[2 * (size_t)k], p->seg_ev[2 * (size_t)k + 1]);
-    if (rc) return rc;
-  }
-  p->seg_timed = n_seg;
-  if (out->top_k > 0) {
-    WuDev v = make_dev(p, &g, out);
-    rc = check_launch(p, fstat::launch_fill_int((int*)v.cand_count, 0, 2, st), "toplist counter reset");
-    if (rc) return rc;
-    rc = check_launch(p, fstat::launch_cand_scan(v, st), "semi-coherent candidate scan");
-    if (rc) return rc;
-    rc = check_launch(p, fstat::launch_top_select(v, st), "toplist selection");
-  }
-  if (rc == FSTAT_OK) queue_drop_check(p, p->status_d, p->status_h, 0, st);
-  return rc;
+  return settle(st, run_segments(p, segs, n_seg, out, st));
 }
 
 int fstat_bins(fstat_plan* p, const fstat_wu* wu, int64_t n, const int32_t* i_sky, const int32_t* i_fd,
@@ -2230,7 +2243,7 @@ int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void
       pick_wave(p, wu, t, wave);
       float ms = 0.f;
       for (int rep = 0; rep < 2; ++rep) {
-        rc = run_demod(p, vt, t, st, false);
+        rc = settle(st, run_demod(p, vt, t, st, false));
         if (rc) return rc;
         hipError_t e = hipEventSynchronize(p->ev1);
         if (e != hipSuccess) return hip_err(p, e, "autotune");
@@ -2262,7 +2275,7 @@ int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void
           p->tiles[bkey] = t;
           float ms = 0.f;
           for (int rep = 0; rep < 2; ++rep) {       // the first call also captures the graph
-            rc = batch_interp(p, wu, 1, out, st);
+            rc = settle(st, batch_interp(p, wu, 1, out, st));
             if (rc) return rc;
             hipError_t e = hipEventSynchronize(p->ev1);
             if (e != hipSuccess) return hip_err(p, e, "autotune");
