@@ -208,14 +208,14 @@ int fstat_compute(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void*
 /* fstat_compute for callers that cannot allocate device memory (code under
  * stream capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same kernels and results as fstat_compute on the same plan, with every
- * piece of device scratch (geometry, coefficients, status record, toplist
- * buffer) in one static device array of FSTAT_NOALLOC_SCRATCH_BYTES that
+ * piece of device scratch (geometry, coefficients, toplist buffer; the status
+ * record of 56 bytes is made with the plan) in one static device array of FSTAT_NOALLOC_SCRATCH_BYTES that
  * each GPU using the library holds until the process ends.  The call itself
  * allocates nothing, device or pinned; create the plan beforehand.  The work
  * unit must fit the array: about 16 B per (sky point, SFT) plus, for the
  * interp kernel, 64 B per (SFT, bin) (32 B with FSTAT_FLAG_COEF16) must stay
- * within FSTAT_NOALLOC_SCRATCH_BYTES less 2 MiB + 4 KiB (the tables, status
- * record and toplist buffer), and top_k within 65536;
+ * within FSTAT_NOALLOC_SCRATCH_BYTES less 2 MiB + 4 KiB (the tables and
+ * the toplist buffer), and top_k within 65536;
  * otherwise FSTAT_E_SIZE with the sizes in fstat_last_error, before anything
  * is launched.  Every call on one GPU shares that GPU's array: calls that
  * overlap in time on one GPU (other threads, other streams, other plans) race

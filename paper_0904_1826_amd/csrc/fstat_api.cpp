@@ -33,6 +33,7 @@ struct fstat_plan {
   fstat::GeoStatus* status_d = nullptr;
   fstat::GeoStatus* status_h = nullptr;  // pinned
   bool status_clear = false;              // status_d was zeroed once; each geometry pass leaves it so
+  uint32_t call = 0;                      // number of the geometry pass (of a batch: passes) queued last, not 0
   double max_abs_tau = 0.0;               // from the last geometry pass
   double max_p = 0.0;                     // max Tdot T, from the last geometry pass
   bool fits16 = false;                    // a block of 16 spindowns fits the slice, from the last geometry pass
@@ -110,8 +111,8 @@ struct fstat_plan {
   std::map<std::vector<int64_t>, hipGraphExec_t> graphs;
   // fault injection (host-side forcing of error paths); force_seg > 0 runs the
   // interp kernels without the global-memory path at that slice width
-  long fail_malloc_at = -1, fail_launch_at = -1;
-  long n_malloc = 0, n_launch = 0;
+  long fail_malloc_at = -1, fail_launch_at = -1, fail_record_at = -1;
+  long n_malloc = 0, n_launch = 0, n_record = 0;
   int force_seg = 0;
   // the demodulation's count of tiles that met an SFT outside their slice, copied to status_h
   // (single unit) or bstat_h[0, drop_units) (batched) after each call and
@@ -143,13 +144,15 @@ int hip_err(fstat_plan* p, hipError_t e, const char* what) {
   return set_err(p, FSTAT_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
-// The Nth allocation / launch fails when FSTAT_FAULT="malloc:N" / "launch:N".
+// The Nth allocation / launch fails when FSTAT_FAULT="malloc:N" / "launch:N";
+// the Nth geometry pass of single-unit calls finds a spoilt record with "record:N".
 void read_fault_env(fstat_plan* p) {
   const char* e = getenv("FSTAT_FAULT");
   if (!e) return;
   long n = 0;
   if (sscanf(e, "malloc:%ld", &n) == 1) p->fail_malloc_at = n;
   if (sscanf(e, "launch:%ld", &n) == 1) p->fail_launch_at = n;
+  if (sscanf(e, "record:%ld", &n) == 1) p->fail_record_at = n;
   if (sscanf(e, "narrow:%ld", &n) == 1 && n >= 8 && n <= 4096) p->force_seg = (int)(n & ~3L);
 }
 
@@ -227,8 +230,8 @@ void queue_drop_check(fstat_plan* p, fstat::GeoStatus* src_d, fstat::GeoStatus* 
 }
 
 // Resets the drop counter of a single-unit call.
-int reset_drops(fstat_plan* p, fstat::GeoStatus* status_d, hipStream_t st) {
-  return check_launch(p, fstat::launch_fill_int((int*)&status_d->dropped, 0, 2, st), "status reset");
+int reset_drops(fstat_plan* p, hipStream_t st) {
+  return check_launch(p, fstat::launch_fill_int((int*)&p->status_d->dropped, 0, 2, st), "status reset");
 }
 
 // Only the interp kernels without the global-memory path can drop tiles.
@@ -237,8 +240,8 @@ bool may_drop(int kernel, const Tile& t) { return kernel == fstat::KERNEL_INTERP
 // The end of a single-unit call: the drop count of a launch that may drop
 // tiles goes to the host; otherwise only the call's end is marked (a wave
 // launch that nothing follows carries ev1 itself).
-void end_call(fstat_plan* p, const Tile& t, int kernel, bool toplist, fstat::GeoStatus* status_d, hipStream_t st) {
-  if (may_drop(kernel, t)) return queue_drop_check(p, status_d, p->status_h, 0, st);
+void end_call(fstat_plan* p, const Tile& t, int kernel, bool toplist, hipStream_t st) {
+  if (may_drop(kernel, t)) return queue_drop_check(p, p->status_d, p->status_h, 0, st);
   p->last_stream = st;
   p->last_event = p->ev1;
   if (kernel == fstat::KERNEL_INTERP && t.wave && !toplist) return;
@@ -772,8 +775,17 @@ double status_bits(unsigned long long b) {
   return t;
 }
 
+uint32_t next_call(fstat_plan* p) {
+  if (++p->call == 0) p->call = 1;
+  return p->call;
+}
+
 // Reads the geometry pass's result of one unit from the host record.
 int read_geometry(fstat_plan* p, const fstat::GeoStatus& g, const char* tag) {
+  if (g.call != p->call) {                 // an earlier pass's: this one found a record that was not clear
+    p->status_clear = false;
+    return set_err(p, FSTAT_E_DEVICE, "%sthe geometry pass published no result", tag);
+  }
   p->max_abs_tau = status_bits(g.max_abs_tau_bits);
   p->max_p = status_bits(g.max_p_bits);
   p->fits16 = (g.flags & fstat::kGeoFits16) != 0;
@@ -787,28 +799,34 @@ int read_geometry(fstat_plan* p, const fstat::GeoStatus& g, const char* tag) {
 // coefficient pass runs.
 constexpr int64_t kFrontBlocks = 4096;
 
-// Enqueues the geometry + band check with the status record status_d; its
-// result is in status_h once ev_geo has fired.  With `stage` (a unit whose sky
-// points may be paired) the sky vectors go to the host with it.  With `coef`
-// the coefficient passes, which do not depend on the check and write only
+// Enqueues the geometry + band check; its result is in status_h once ev_geo
+// has fired.  The record is the plan's own, also for calls on the static
+// scratch: it has to be clear when a pass starts, and calls of other plans that
+// overlap on that scratch must not leave it otherwise.  With `stage` (a unit
+// whose sky points may be paired) the sky vectors go to the host with it.  With
+// `coef` the coefficient passes, which do not depend on the check and write only
 // scratch, are queued too, so that the device works while the host waits.
-int queue_geometry(fstat_plan* p, const WuDev& v, fstat::GeoStatus* status_d, hipStream_t st, const fstat_wu* stage,
-                   bool coef) {
+int queue_geometry(fstat_plan* p, WuDev& v, hipStream_t st, const fstat_wu* stage, bool coef) {
   p->sky_staged = nullptr;
+  v.call = next_call(p);
   const bool by_kernel = stage && stage->n_sky <= kSkyByKernel;
   int rc = by_kernel ? stage_sky(p, stage, false, st) : FSTAT_OK;
   if (rc) return rc;
-  if (status_d == p->status_d && !p->status_clear) {
-    const hipError_t e = fstat::launch_fill_int((int*)status_d, 0, (int)(sizeof(fstat::GeoStatus) / sizeof(int)), st);
+  if (!p->status_clear) {
+    const hipError_t e = fstat::launch_fill_int((int*)p->status_d, 0, (int)(sizeof(fstat::GeoStatus) / sizeof(int)), st);
     if (e != hipSuccess) return hip_err(p, e, "status reset");
     p->status_clear = true;
+  }
+  if (++p->n_record == p->fail_record_at) {
+    const hipError_t e = fstat::launch_fill_int((int*)&p->status_d->arrived, 1 << 30, 1, st);
+    if (e != hipSuccess) return hip_err(p, e, "status reset");
   }
   const bool copy = stage && !by_kernel;
   double* sky = by_kernel ? p->sky_h : nullptr;
   hipEvent_t done = copy ? nullptr : p->ev_geo;
   const bool front = coef && !v.coef16 && v.n_sky <= 256 && fstat::coef_blocks(v) <= kFrontBlocks;
-  rc = check_launch(p, front ? fstat::launch_front(v, status_d, p->status_h, sky, st, done)
-                             : fstat::launch_geometry(v, status_d, p->status_h, sky, st, done),
+  rc = check_launch(p, front ? fstat::launch_front(v, p->status_d, p->status_h, sky, st, done)
+                             : fstat::launch_geometry(v, p->status_d, p->status_h, sky, st, done),
                     "geometry kernel");
   if (rc) return rc;
   // the two passes of one launch are two steps to the fault injection
@@ -831,8 +849,8 @@ int wait_geometry(fstat_plan* p, int idx) {
   return read_geometry(p, *p->status_h, tag);
 }
 
-int run_geometry(fstat_plan* p, const WuDev& v, hipStream_t st, int idx) {
-  const int rc = queue_geometry(p, v, p->status_d, st, nullptr, false);
+int run_geometry(fstat_plan* p, WuDev& v, hipStream_t st, int idx) {
+  const int rc = queue_geometry(p, v, st, nullptr, false);
   return rc ? rc : wait_geometry(p, idx);
 }
 
@@ -861,12 +879,12 @@ int run_demod(fstat_plan* p, const WuDev& v, const Tile& t, hipStream_t st, bool
 }
 
 // The wave kernel queued behind the geometry pass, gated by its result.
-int queue_wave_ahead(fstat_plan* p, WuDev v, fstat::GeoStatus* status_d, hipStream_t st) {
+int queue_wave_ahead(fstat_plan* p, WuDev v, hipStream_t st) {
   Tile t = wave_tile();
   t.wave = 1;
-  v.gate = &status_d->gate;
+  v.gate = &p->status_d->gate;
   const int rc = run_demod(p, v, t, st, true);
-  if (rc == FSTAT_OK) end_call(p, t, fstat::KERNEL_INTERP, false, status_d, st);
+  if (rc == FSTAT_OK) end_call(p, t, fstat::KERNEL_INTERP, false, st);
   return rc;
 }
 
@@ -917,8 +935,10 @@ int ensure_pinned_pair(fstat_plan* p, T** dev, T** host, size_t* cap, size_t nee
 // at sky_off[k] points) the sky vectors of the units that may be paired too.
 int batch_geometry(fstat_plan* p, const fstat_wu* wus, const fstat_out* outs, int k0, int k1, char* geo_base,
                    const std::vector<size_t>& offs, double* sky, const std::vector<int64_t>& sky_off, hipStream_t st) {
+  const uint32_t call = next_call(p);
   for (int k = k0; k < k1; ++k) {
     WuDev v = make_dev(p, &wus[k], &outs[k]);
+    v.call = call;
     const WuScratch sc = wu_scratch(p, &wus[k], 0);   // geometry and A,B,C,D come first either way
     v.geo = (double2*)(geo_base + offs[k]);
     v.abcd = (double4*)(geo_base + offs[k] + sc.geo);
@@ -1721,15 +1741,14 @@ int batch_interp(fstat_plan* p, const fstat_wu* wus, int n, const fstat_out* out
 // One validated unit, its scratch in place: check, coefficients, demodulation.
 // On the static scratch: no carried Fa, Fb, so one launch over all SFTs, and no
 // pairs, whose table is allocated.
-int run_unit(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, WuDev v, fstat::GeoStatus* status,
-             bool static_scratch, hipStream_t st) {
+int run_unit(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, WuDev v, bool static_scratch, hipStream_t st) {
   const int kernel = resolved_kernel(p);
   const bool interp = kernel == fstat::KERNEL_INTERP, pair = !static_scratch && may_pair(p, wu);
-  int rc = queue_geometry(p, v, status, st, pair ? wu : nullptr, interp);
+  int rc = queue_geometry(p, v, st, pair ? wu : nullptr, interp);
   if (rc) return rc;
   const bool ahead = wave_ahead(p, wu, out, pair);
   if (ahead) {
-    rc = queue_wave_ahead(p, v, status, st);
+    rc = queue_wave_ahead(p, v, st);
     if (rc) return rc;
   }
   rc = wait_geometry(p, -1);
@@ -1740,9 +1759,9 @@ int run_unit(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, WuDev v, f
   if (static_scratch) t.sblock = 0;
   else if ((rc = prepare_pairs(p, wu, v, t, st, dflt))) return rc;
   pick_wave(p, wu, t, dflt);
-  if (may_drop(kernel, t)) rc = reset_drops(p, status, st);
+  if (may_drop(kernel, t)) rc = reset_drops(p, st);
   if (rc == FSTAT_OK) rc = run_demod(p, v, t, st, interp);
-  if (rc == FSTAT_OK) end_call(p, t, kernel, out->top_k > 0, status, st);
+  if (rc == FSTAT_OK) end_call(p, t, kernel, out->top_k > 0, st);
   return rc;
 }
 
@@ -1759,7 +1778,7 @@ int batch_direct(fstat_plan* p, const fstat_wu* wus, int n, const fstat_out* out
     rc = run_demod(p, v, pick_tile(p, &wus[k]), st, false);
     if (rc) return rc;
   }
-  end_call(p, Tile{}, fstat::KERNEL_DIRECT, true, p->status_d, st);
+  end_call(p, Tile{}, fstat::KERNEL_DIRECT, true, st);
   return FSTAT_OK;
 }
 
@@ -1768,7 +1787,7 @@ int run_segments(fstat_plan* p, const fstat_wu* segs, int n_seg, const fstat_out
   const fstat_wu& g = segs[0];
   int rc = ensure_toplist(p, out);
   if (rc) return rc;
-  rc = reset_drops(p, p->status_d, st);
+  rc = reset_drops(p, st);
   if (rc) return rc;
   fstat_out o = *out;
   o.top_k = 0;                       // the toplist is taken of the sum, after the last segment
@@ -1816,8 +1835,10 @@ int run_segments(fstat_plan* p, const fstat_wu* segs, int n_seg, const fstat_out
                     "status reset");
   if (rc) return rc;
   std::vector<WuDev> vs((size_t)n_seg);
+  const uint32_t call = next_call(p);
   for (int k = 0; k < n_seg; ++k) {
     WuDev v = make_dev(p, &segs[k], &o);
+    v.call = call;
     char* base = (char*)p->seg_arena + goff[k];
     v.geo = (double2*)base;
     v.abcd = (double4*)(base + align256((size_t)n * segs[k].n_sft * sizeof(double2)));
@@ -1844,9 +1865,10 @@ int run_segments(fstat_plan* p, const fstat_wu* segs, int n_seg, const fstat_out
   if (e == hipSuccess) e = hipEventSynchronize(p->ev_geo);
   if (e != hipSuccess) return hip_err(p, e, "geometry kernel");
   for (int k = 0; k < n_seg; ++k) {
-    const int bits = p->bstat_h[k].flags;
-    if (bits & 1) return set_err(p, FSTAT_E_BAND, "segment %d: a Dirichlet window [k*-D+1, k*+D] leaves the stored band", k);
-    if (bits & 2) return set_err(p, FSTAT_E_ARG, "segment %d: antenna-pattern matrix is singular (A B - C^2 <= 0)", k);
+    char tag[32];
+    snprintf(tag, sizeof tag, "segment %d: ", k);
+    rc = read_geometry(p, p->bstat_h[k], tag);
+    if (rc) return rc;
   }
   for (int k = 0; k < n_seg; ++k) {
     WuDev v = vs[(size_t)k];
@@ -1996,7 +2018,7 @@ int fstat_compute(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void*
   if (rc) return rc;
   rc = ensure_toplist(p, out);
   if (rc) return rc;
-  return settle(st, run_unit(p, wu, out, make_dev(p, wu, out), p->status_d, false, st));
+  return settle(st, run_unit(p, wu, out, make_dev(p, wu, out), false, st));
 }
 
 int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void* stream) {
@@ -2028,7 +2050,6 @@ int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* ou
     return set_err(p, FSTAT_E_SIZE, "fstat_compute_noalloc: top_k %d exceeds the static toplist capacity %lld",
                    out->top_k, (long long)cap);
   hipStream_t st = (hipStream_t)stream;
-  fstat::GeoStatus* status = (fstat::GeoStatus*)(base + fstat::kStaticStatusOff);
   WuDev v = make_dev(p, wu, out);
   char* work = base + fstat::kStaticWorkOff;
   v.geo = (double2*)work;
@@ -2039,13 +2060,12 @@ int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* ou
   const int c = coef16(p) ? 1 : 0;
   v.ctab = interp ? (const double*)(base + g_tab_off[c][wu->dterms]) : nullptr;
   v.csum = g_tab_csum[c][wu->dterms];
-  v.dropped = &status->dropped;
   v.cand_cap = cap;
   if (out->top_k > 0) {
     v.cand = (uint4*)(base + fstat::kStaticCandOff);
     v.cand_count = (unsigned long long*)(base + fstat::kStaticCountOff);
   }
-  return settle(st, run_unit(p, wu, out, v, status, true, st));
+  return settle(st, run_unit(p, wu, out, v, true, st));
 }
 
 int fstat_batch_compute(fstat_plan* p, const fstat_wu* wus, int32_t n_wu, const fstat_out* outs, void* stream) {
@@ -2214,7 +2234,7 @@ int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void
     if (rc) return rc;
     rc = ensure_toplist(p, out);
     if (rc) return rc;
-    rc = reset_drops(p, p->status_d, st);
+    rc = reset_drops(p, st);
     if (rc) return rc;
     WuDev v = make_dev(p, wu, out);
     rc = run_geometry(p, v, st, -1);

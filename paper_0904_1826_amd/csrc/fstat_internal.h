@@ -47,9 +47,13 @@ struct WuDev {
   // with an SFT whose windows were not all inside the LDS slice are counted
   // here, and their outputs set to NaN; NULL: not counted
   unsigned long long* dropped;
-  const int* gate;         // wave kernel: NULL, or the geometry pass's gate, 0: write nothing
+  // wave kernel: NULL, or the geometry pass's gate, which holds `call` if the
+  // pass passed its checks; else nothing is written.  call: number of the
+  // host's call to the geometry pass, which publishes it with its result
+  const uint32_t* gate;
   int64_t n_sft, n_bins, k_first, n_sky, n_f, n_fd;
   double t_sft, f0, df, fdot0, dfdot, t_ref;
+  uint32_t call;
   int32_t dterms;
   int32_t storage;
   int32_t phase_mode;      // 0: frac(phi) in FP64; 1: in double-FP32 (split) products
@@ -139,19 +143,18 @@ struct GeoStatus {
   unsigned long long max_v_bits;         // max |v| over SFTs (units of c), as FP64 bits
   unsigned long long max_r_bits;         // max |r| over SFTs (light-seconds), as FP64 bits
   unsigned long long dropped;            // demodulation: tiles with an SFT outside the slice
-  int gate;                   // the last pass passed its checks and set kGeoFits16
-  int pad;
+  uint32_t gate;              // call number of the last pass if it passed its checks and set kGeoFits16, else 0
+  uint32_t call;              // host copy: call number of the pass
 };
 // A tile of 16 spindowns per thread holds every window in its slice.
 constexpr int kGeoFits16 = 4;
 
 // Static scratch of the no-allocation entry point: one array of this many
 // bytes per device, laid out as the polynomial tables of every Dterms in both
-// bases (kStaticTabBytes), the status record and toplist counter, the
-// toplist buffer (kStaticCands entries) and the work region.
+// bases (kStaticTabBytes), the toplist counter, the toplist buffer
+// (kStaticCands entries) and the work region.
 constexpr size_t kStaticScratchBytes = (size_t)128 << 20;
 constexpr size_t kStaticTabBytes = (size_t)1 << 20;
-constexpr size_t kStaticStatusOff = kStaticTabBytes;            // GeoStatus
 constexpr size_t kStaticCountOff = kStaticTabBytes + 256;       // toplist counter (2 x u64)
 constexpr int64_t kStaticCands = 65536;
 constexpr size_t kStaticCandOff = kStaticTabBytes + 4096;       // kStaticCands x 16 B

@@ -289,12 +289,13 @@ __device__ __forceinline__ void geometry_blocks(const WuDev& w, GeoStatus* statu
   const double spread = (255.0 * w.df + fabs(w.dfdot) * 15.0 * __longlong_as_double((long long)tb)) *
                         __longlong_as_double((long long)pb);
   if (spread <= 255.0 + (double)((w.coef16 ? kSegMax16 : kSegMax) - 262)) flags |= kGeoFits16;
-  status->gate = flags == kGeoFits16 ? 1 : 0;
+  status->gate = flags == kGeoFits16 ? w.call : 0u;
   host->max_abs_tau_bits = tb;
   host->max_p_bits = pb;
   host->max_v_bits = atomicExch(&status->max_v_bits, 0ull);
   host->max_r_bits = atomicExch(&status->max_r_bits, 0ull);
   host->flags = flags;
+  host->call = w.call;
   atomicExch(&status->arrived, 0u);
   __threadfence_system();
 }
@@ -1551,7 +1552,7 @@ __global__ __launch_bounds__(kThreads, 3) void demod_wave_kernel(WuDev w) {
   // alternate between two register sets
   static_assert(64 % (2 * kAhead) == 0, "a block holds whole pairs of groups");
   fetch(0);
-  if (w.gate && !*w.gate) return;                  // launched ahead of the check, which failed
+  if (w.gate && *w.gate != w.call) return;                  // launched ahead of the check, which failed
   publish(0);
   if (n > 64) fetch(64);
   Group ga, gb;
