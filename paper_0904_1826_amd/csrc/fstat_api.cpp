@@ -1148,22 +1148,30 @@ bool pairs_apply(const fstat_plan* p, const fstat_wu* wu, const Tile& t) {
 
 bool wave_beats_tile(const fstat_plan* p, const fstat_wu* wu, bool paired);
 
-// Tiles of two sky points take 1.91 times as long per SFT as tiles of one
-// (2000 sky points x 8 spindowns x 3600 frequencies x 400 SFTs, all of them
-// paired: 20.0 against 21.1 ms), 1.80 in the form that shares no coefficients
-// (1000 x 5 x 3600 x 400 at a step of 0.37 bins: 8.15 against 8.79 ms), so they
-// pay if few points go without a partner.
-double pair_cost(bool shared) { return shared ? 1.91 : 1.80; }
-bool pairs_pay(int64_t np, int64_t n, bool shared) { return pair_cost(shared) * (double)np <= (double)n; }
+// Time per SFT of a tile of two sky points in that of one, by spindowns per
+// thread, in the forms with and without shared coefficients (400 SFTs x 3600
+// frequencies; paired, single): 8: 1000 sky points 10.29, 10.63 ms and (step
+// 0.5 bins) 11.48, 11.69; 600 with 318 and 316 tiles 6.72, 6.51 and 7.34, 7.12;
+// 7: 1000 points 9.23, 9.68 and 10.34, 10.79; 6: 8.21, 8.84 and 9.26, 9.66; 5:
+// 7.31, 8.03 and 7.98, 8.84; 4: 6.07, 7.57 and 6.43, 7.75.  So pairs pay if few
+// points go without a partner.
+double pair_cost(int nfd, bool shared) {
+  static const double kShared[] = {1.60, 1.82, 1.85, 1.90, 1.92}, kPlain[] = {1.65, 1.82, 1.91, 1.91, 1.95};
+  const int i = (nfd < 4 ? 4 : nfd > 8 ? 8 : nfd) - 4;
+  return shared ? kShared[i] : kPlain[i];
+}
+bool pairs_pay(int64_t np, const fstat_wu* wu, bool shared) {
+  return pair_cost((int)std::min<int64_t>(wu->n_fd, 8), shared) * (double)np <= (double)wu->n_sky;
+}
 
 // Time of a completed tile's launches in the time of one (sky point, spindown)
-// slot on a full device: the work-groups run in rounds of `per` on each of the
-// 256 CUs, and a last round of k of them takes about 0.2 + 0.8 k / per of a
-// full one, since what is left runs faster with fewer beside it.  Measured
+// slot on a full device: the work-groups run in rounds of `per` on each CU (256
+// of them where measured), and a last round of k of them takes about 0.2 + 0.8
+// k / per of a full one, since what is left runs faster with fewer beside it.  Measured
 // (paired, single; 400 SFTs, 8 spindowns): 150 sky points x 3600 frequencies,
-// 1125 paired work-groups, 2.06, 1.96 ms (model: +5 %); 200, 2.31, 2.43 (-4 %);
+// 1125 paired work-groups, 2.06, 1.96 ms (model: +4 %); 200, 2.31, 2.43 (-4 %);
 // 350, 4.07, 4.05 (0 %); 61 x 5 spindowns x 3001 x 701 SFTs, 372, 1.35, 1.09.
-double grid_slots(const fstat_wu* wu, const Tile& t, int64_t np) {
+double grid_slots(const fstat_plan* p, const fstat_wu* wu, const Tile& t, int64_t np) {
   const int64_t n_ft = (wu->n_f + fstat::kThreads - 1) / fstat::kThreads;
   const bool one = std::all_of(t.fd_split, t.fd_split + fstat::kSplitSizes, [](int32_t x) { return x == 0; });
   double sum = 0.0;
@@ -1172,10 +1180,12 @@ double grid_slots(const fstat_wu* wu, const Tile& t, int64_t np) {
     const int64_t n = one ? (nfd == 8 ? wu->n_fd : 0) : t.fd_split[i];
     if (n <= 0) continue;
     const bool pair = np > 0 && nfd <= 8;
-    const int64_t round = 256 * (pair ? (nfd == 4 ? 4 : 3) : nfd == 16 ? 3 : 4);
+    const int64_t round = p->cu_count * (pair ? (nfd == 4 ? 4 : 3) : nfd == 16 ? 3 : 4);
     const int64_t groups = n_ft * ((n + nfd - 1) / nfd) * (pair ? np : wu->n_sky);
-    const double tail = groups % round ? 0.2 + 0.8 * (double)((groups % round + 255) / 256 * 256) / (double)round : 0.0;
-    sum += ((double)(groups / round) + tail) * (double)round * nfd * (pair ? pair_cost(t.fast >= fstat::kPathShared) : 1.0);
+    const int64_t last = (groups % round + p->cu_count - 1) / p->cu_count * p->cu_count;
+    const double tail = last > 0 ? 0.2 + 0.8 * (double)last / (double)round : 0.0;
+    sum += ((double)(groups / round) + tail) * (double)round * nfd *
+           (pair ? pair_cost(nfd, t.fast >= fstat::kPathShared) : 1.0);
   }
   return sum;
 }
@@ -1196,7 +1206,7 @@ int pair_sky(fstat_plan* p, const fstat_wu* wu, WuDev& v, Tile& t, hipStream_t s
   if (!width) return FSTAT_OK;
   // the split with the costs of paired tiles; pairs serve its ranges of at most 8
   const Tile tp = complete_tile(p, wu, t, true);
-  if (default_tile_used && !wave_beats_tile(p, wu, true) && grid_slots(wu, tp, np) > grid_slots(wu, t, 0))
+  if (default_tile_used && !wave_beats_tile(p, wu, true) && grid_slots(p, wu, tp, np) > grid_slots(p, wu, t, 0))
     return FSTAT_OK;
   bool small = std::all_of(tp.fd_split, tp.fd_split + fstat::kSplitSizes, [](int32_t x) { return x == 0; });
   for (int i = 0; i < fstat::kSplitSizes; ++i) small = small || (fstat::split_nfd(i) <= 8 && tp.fd_split[i] > 0);
@@ -1235,9 +1245,10 @@ int prepare_pairs(fstat_plan* p, const fstat_wu* wu, WuDev& v, Tile& t, hipStrea
   return pair_sky(p, wu, v, t, st, default_tile_used, *p->status_h, p->sky_h, p->pairs_h, p->pairs_d);
 }
 
-// Whether demod_wave_kernel is expected to beat the interp tile `t` (already
-// completed for the unit) on this unit.  Both are modelled as time per SFT,
-// measured on 1 to 900 sky points x 1 to 40 spindowns x 1800 frequencies:
+// Whether demod_wave_kernel is expected to beat the unit's interp tile (with
+// pairs of sky points if `paired`).  For three spindowns or more both are
+// modelled as time per SFT, measured on 1 to 900 sky points x 1 to 40 spindowns
+// x 1800 frequencies:
 // - the wave kernel takes 0.11 us + 2.2e-6 us per template (1.25e-6 with FP16
 //   coefficients, whose loads are half as wide): 0.24 us at 5e4 templates,
 //   1.04 at 4e5, 1.98 at 8.6e5 (4.5e11 pairs/s, the rate of its 64-byte loads);
@@ -1250,20 +1261,34 @@ int prepare_pairs(fstat_plan* p, const fstat_wu* wu, WuDev& v, Tile& t, hipStrea
 // against 1.68 at 7.2e5), 16 at 8.0e5 (1.94 against 1.32 us at 5.7e5, 1.89
 // against 1.98 at 8.6e5) and 24 = 16 + 8 at 1.4e6 (3.04 against 2.72 us at
 // 1.2e6, 3.05 against 3.52 at 1.55e6); 8 with FP16 coefficients at 9.8e5 (1.40
-// against 1.18 us at 8.6e5).  One or two spindowns have no
-// efficient tile (4.1 against 2.2 us at 8e5 templates x 1 spindown, 7.1 against
-// 6.7 at 2.9e6 x 2).  Units whose block of 16 spindowns outgrows the slice keep
-// the tiles: their spindowns share few cache lines.
+// against 1.18 us at 8.6e5).  Units whose block of 16 spindowns outgrows the
+// slice keep the tiles: their spindowns share few cache lines.
+// One or two spindowns have a poor tile and nothing to share between the waves
+// of a work-group, so that these drift apart over the SFTs and read the
+// coefficients from ever further away: in units of many SFTs with a step near
+// the bins', the tiles win by up to 2.4.  Time per SFT (wave, tile), FP32
+// coefficients, 3600 frequencies: 1 spindown, step 1, 2.4e6 templates: 250 SFTs
+// 6.4, 8.1 us, 350 7.5, 7.9, 500 11.9, 7.8, 1500 17.2, 8.6; step 0.75: 800 SFTs
+// 7.8, 7.7, 1500 12.7, 8.5; step 0.5: 1500 4.6, 7.9; 3e5 templates, step 1, 1500
+// SFTs 1.38, 1.64.  2 spindowns, 300 SFTs, step 1: 3e5 templates 0.81, 0.89, 6e5
+// 1.55, 1.56, 2.4e6 5.9, 4.7; 1500 SFTs, step 0.5: 6e5 1.33, 1.47, 2.4e6 4.5, 4.3
+// (30000 frequencies: 6e5 1.9, 1.9, 2.4e6 7.0, 4.6).  FP16: 1 spindown, 1500 SFTs,
+// step 1: 3e5 0.58, 0.82, 1.2e6 3.3, 2.8; 400 SFTs 4e6 5.7, 8.9; 2 spindowns, 400
+// SFTs 5.3, 5.5, 1500 SFTs 11.1, 5.2, step 0.75 4.8, 5.2.
 bool wave_beats_tile(const fstat_plan* p, const fstat_wu* wu, bool paired) {
   if (resolved_kernel(p) != fstat::KERNEL_INTERP || p->force_seg > 0) return false;
-  if (wu->n_fd <= 2) return true;
+  const double templates = (double)wu->n_sky * (double)wu->n_fd * (double)((wu->n_f + 63) / 64 * 64);
+  if (wu->n_fd <= 2) {
+    const double step = wu->df * wu->t_sft, drift = (double)wu->n_sft * (step - 0.5);
+    if (coef16(p)) return templates <= 4e5 || drift <= 300.0;
+    return wu->n_fd == 1 ? templates <= 4e5 || drift <= 150.0 : templates <= 3e5 || (drift <= 0.0 && templates <= 1e6);
+  }
   static const double kFloor[17] = {0.0,  0.0, 0.0, 0.0, 0.98, 1.10, 1.12, 1.15, 1.34,
                                     0.0, 0.0, 0.0, 0.0, 0.0,  0.0,  0.0,  1.87};
   const FdSplit sp = split_spindowns(wu->n_fd, coef16(p) ? (1u << 8) | (1u << 4) : kAllSplitSizes, paired);
   double tile_us = 0.0;
   for (int i = 0; i < fstat::kSplitSizes; ++i)
     if (sp.n[i] > 0) tile_us += kFloor[fstat::split_nfd(i)];
-  const double templates = (double)wu->n_sky * (double)wu->n_fd * (double)((wu->n_f + 63) / 64 * 64);
   return 0.11 + (coef16(p) ? 1.25e-6 : 2.2e-6) * templates < tile_us;
 }
 
@@ -1342,7 +1367,7 @@ int batch_unit_shapes(fstat_plan* p, const fstat_wu* wus, const std::vector<int>
     us[q].pair_width =
         make_pairs(&wus[k], p->bstat_h[k], p->sky_h + 3 * sky_off[k], p->pairs_h + sky_off[k], &us[q].n_pairs);
     if (us[q].pair_width &&
-        !pairs_pay(us[q].n_pairs, wus[k].n_sky, slots_share(&wus[k], status_tau(p->bstat_h[k]))))
+        !pairs_pay(us[q].n_pairs, &wus[k], slots_share(&wus[k], status_tau(p->bstat_h[k]))))
       us[q].pair_width = 0;
     if (!us[q].pair_width) continue;
     const hipError_t e = hipMemcpyAsync(p->pairs_d + sky_off[k], p->pairs_h + sky_off[k],
