@@ -202,11 +202,13 @@ int fstat_plan_create(fstat_plan** out, const fstat_desc* d);
  * demodulation kernel, which writes `out` asynchronously.  Between the two, the interp kernel's host side copies the
  * sky vectors back (one more short wait) to pair neighbouring sky points
  * into tiles of two where the slice can hold both (fstat_last_tile reports
- * the shape that ran).  Returns after (2) is enqueued. */
+ * the shape that ran).  Returns after (2) is enqueued.  A stream under capture
+ * is refused (FSTAT_E_DEVICE, nothing queued; so by every call that waits for
+ * a band check): the check would be made only when the graph runs. */
 int fstat_compute(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void* stream);
 
-/* fstat_compute for callers that cannot allocate device memory (code under
- * stream capture, tight serving loops, harnesses that forbid hipMalloc): the
+/* fstat_compute for callers that cannot allocate device memory (while
+ * another stream is under capture, tight serving loops, harnesses that forbid hipMalloc): the
  * same kernels and results as fstat_compute on the same plan, with every
  * piece of device scratch (geometry, coefficients, toplist buffer; the status
  * record of 56 bytes is made with the plan) in one static device array of FSTAT_NOALLOC_SCRATCH_BYTES that

@@ -182,9 +182,15 @@ int check_launch(fstat_plan* p, hipError_t e, const char* what) {
   return FSTAT_OK;
 }
 
-// The previous call's tiles that met an SFT outside their slice, once the copy has landed:
-// an error naming them (their templates' outputs are NaN), else FSTAT_OK.
-int check_prev_drops(fstat_plan* p, hipStream_t st) {
+// The start of a call on the plan.  A stream under capture is refused: the call
+// would read a band check that its geometry pass has yet to make.  Then, the
+// previous call's tiles that met an SFT outside their slice, once the copy has
+// landed: an error naming them (their templates' outputs are NaN), else FSTAT_OK.
+int begin_call(fstat_plan* p, hipStream_t st) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (st && hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();   // NULL: never captured
+  if (capture != hipStreamCaptureStatusNone)
+    return set_err(p, FSTAT_E_DEVICE, "the stream is under capture, and the call waits for its band check");
   // (the per-thread stream is another one in each thread)
   if (p->last_event && (st != p->last_stream || st == hipStreamPerThread)) (void)hipEventSynchronize(p->last_event);
   if (!p->drop_pending) return FSTAT_OK;
@@ -2033,7 +2039,7 @@ int fstat_compute(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void*
   p->timed = false;
   p->ms_prev = 0.0;
   p->seg_timed = 0;
-  int rc = check_prev_drops(p, (hipStream_t)stream);
+  int rc = begin_call(p, (hipStream_t)stream);
   if (rc) return rc;
   rc = validate_wu(p, wu, out, -1);
   if (rc) return rc;
@@ -2052,7 +2058,7 @@ int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* ou
   p->timed = false;
   p->ms_prev = 0.0;
   p->seg_timed = 0;
-  int rc = check_prev_drops(p, (hipStream_t)stream);
+  int rc = begin_call(p, (hipStream_t)stream);
   if (rc) return rc;
   rc = validate_wu(p, wu, out, -1);
   if (rc) return rc;
@@ -2099,7 +2105,7 @@ int fstat_batch_compute(fstat_plan* p, const fstat_wu* wus, int32_t n_wu, const 
   p->timed = false;
   p->ms_prev = 0.0;
   p->seg_timed = 0;
-  int rc0 = check_prev_drops(p, (hipStream_t)stream);
+  int rc0 = begin_call(p, (hipStream_t)stream);
   if (rc0) return rc0;
   if (n_wu < 0 || (n_wu > 0 && (!wus || !outs))) return set_err(p, FSTAT_E_ARG, "bad work-unit list");
   for (int k = 0; k < n_wu; ++k) {
@@ -2119,7 +2125,7 @@ int fstat_semicoherent(fstat_plan* p, const fstat_wu* segs, int32_t n_seg, const
   p->timed = false;
   p->ms_prev = 0.0;
   p->seg_timed = 0;
-  int rc0 = check_prev_drops(p, (hipStream_t)stream);
+  int rc0 = begin_call(p, (hipStream_t)stream);
   if (rc0) return rc0;
   if (n_seg < 1 || !segs || !out) return set_err(p, FSTAT_E_ARG, "semi-coherent: need n_seg >= 1 segments and an output");
   if (!out->twoF) return set_err(p, FSTAT_E_ARG, "semi-coherent: the twoF output holds the sum and is required");
@@ -2216,7 +2222,7 @@ int fstat_detector_inputs(fstat_plan* p, const fstat_earth* earth, int32_t n_sit
 int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void* stream, const char* cache_path) {
   if (!p) return FSTAT_E_ARG;
   p->err[0] = 0;
-  int rc = check_prev_drops(p, (hipStream_t)stream);
+  int rc = begin_call(p, (hipStream_t)stream);
   if (rc) return rc;
   rc = validate_wu(p, wu, out, -1);
   if (rc) return rc;
@@ -2309,7 +2315,7 @@ int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void
   if (!have_b) {
     // the batched launch shape, timed on this unit as a batch of one: the
     // spindown blocking, tiles per chunk of the per-XCD queues, SFTs per launch
-    rc = check_prev_drops(p, (hipStream_t)stream);
+    rc = begin_call(p, (hipStream_t)stream);
     if (rc) return rc;
     float best = 1e30f;
     Tile best_t = default_batch_tile();
@@ -2326,7 +2332,7 @@ int fstat_autotune(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void
             if (e != hipSuccess) return hip_err(p, e, "autotune");
             (void)hipEventElapsedTime(&ms, p->ev0, p->ev1);
           }
-          rc = check_prev_drops(p, (hipStream_t)stream);
+          rc = begin_call(p, (hipStream_t)stream);
           if (rc) return rc;
           if (verbose)
             fprintf(stderr, "[fstat autotune] %s nfd=%d chunk=%d sblock=%d: %.3f ms\n", bkey.c_str(), nfd, chunk, sb,
