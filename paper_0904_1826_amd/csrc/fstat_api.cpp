@@ -860,13 +860,18 @@ int run_geometry(fstat_plan* p, WuDev& v, hipStream_t st, int idx) {
   return rc ? rc : wait_geometry(p, idx);
 }
 
+// Keeps the launch shape for fstat_last_tile.
+void note_shape(fstat_plan* p, const WuDev& v, const Tile& t) {
+  p->have_last = true;
+  p->last_tile = t;
+  p->last_sky_tiles = v.n_pairs > 0 && t.pair_seg > 0 ? v.n_pairs : v.n_sky;
+}
+
 // With coef_done the coefficient passes are already queued.
 int run_demod(fstat_plan* p, const WuDev& v, const Tile& t, hipStream_t st, bool coef_done, hipEvent_t e0 = nullptr,
               hipEvent_t e1 = nullptr) {
   const int kernel = resolved_kernel(p);
-  p->have_last = true;                 // (a launch that its gate ends is reported too)
-  p->last_tile = t;
-  p->last_sky_tiles = v.n_pairs > 0 && t.pair_seg > 0 ? v.n_pairs : v.n_sky;
+  if (!v.gate) note_shape(p, v, t);      // a gated launch may write nothing
   if (kernel == fstat::KERNEL_INTERP && !coef_done) {
     int rc = run_coef(p, v, st);
     if (rc) return rc;
@@ -885,9 +890,7 @@ int run_demod(fstat_plan* p, const WuDev& v, const Tile& t, hipStream_t st, bool
 }
 
 // The wave kernel queued behind the geometry pass, gated by its result.
-int queue_wave_ahead(fstat_plan* p, WuDev v, hipStream_t st) {
-  Tile t = wave_tile();
-  t.wave = 1;
+int queue_wave_ahead(fstat_plan* p, WuDev v, const Tile& t, hipStream_t st) {
   v.gate = &p->status_d->gate;
   const int rc = run_demod(p, v, t, st, true);
   if (rc == FSTAT_OK) end_call(p, t, fstat::KERNEL_INTERP, false, st);
@@ -1778,15 +1781,18 @@ int run_unit(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, WuDev v, b
   int rc = queue_geometry(p, v, st, pair ? wu : nullptr, interp);
   if (rc) return rc;
   const bool ahead = wave_ahead(p, wu, out, pair);
+  Tile t = wave_tile();
+  t.wave = 1;
   if (ahead) {
-    rc = queue_wave_ahead(p, v, st);
+    rc = queue_wave_ahead(p, v, t, st);
     if (rc) return rc;
   }
   rc = wait_geometry(p, -1);
   if (rc) p->timed = false;
+  else if (ahead && p->fits16) note_shape(p, v, t);
   if (rc || (ahead && p->fits16)) return rc;
   bool dflt = false;
-  Tile t = pick_tile(p, wu, &dflt);
+  t = pick_tile(p, wu, &dflt);
   if (static_scratch) t.sblock = 0;
   else if ((rc = prepare_pairs(p, wu, v, t, st, dflt))) return rc;
   pick_wave(p, wu, t, dflt);
