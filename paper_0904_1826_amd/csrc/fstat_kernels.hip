@@ -1629,16 +1629,24 @@ __device__ __forceinline__ int4 top_entry(const WuDev& w, uint4 c) {
 // over the chunks of the better entries there (a binary search each), given up
 // once it reaches top_k.  A bitonic sort over the whole capacity takes 136
 // launches at 65536 entries, 0.54 ms whatever the count.
+// A rank walks up to one chunk after the other, so that the best entries of a
+// large segment take long (1.6e7 candidates: 31, 126 and 280 ms for the best
+// 20, 1000 and 60000, the bitonic sort 22; 8.6e5: 0.9, 1.0 and 1.6 ms against
+// 1.4): segments that hold more than kRankHeld are left to the bitonic sort,
+// except where the capacity is at most kRankCap and the toplist short.
 constexpr int kSortChunk = 4096;
+constexpr int64_t kRankHeld = (int64_t)1 << 18;
+constexpr int64_t kRankCap = (int64_t)1 << 20;
+constexpr int kRankShort = 4096;
 constexpr int kSortThreads = 1024;
 
 template <class Seg>
-__global__ __launch_bounds__(kSortThreads) void cand_chunk_kernel(Seg seg, uint4* cand, int64_t cap) {
+__global__ __launch_bounds__(kSortThreads) void cand_chunk_kernel(Seg seg, uint4* cand, int64_t cap, int64_t limit) {
   const int q = blockIdx.y;
   const WuDev& w = seg.unit(q);
   if (!w.cand || w.top_k <= 0) return;
   const int64_t n = cand_held(w, cap), c0 = (int64_t)blockIdx.x * kSortChunk;
-  if (blockIdx.x > 0 && c0 >= n) return;
+  if (n > limit || (blockIdx.x > 0 && c0 >= n)) return;
   __shared__ uint4 x[kSortChunk];
   uint4* src = cand + (int64_t)q * cap + c0;
   const int m = (int)(n - c0 < kSortChunk ? n - c0 : kSortChunk);
@@ -1669,12 +1677,12 @@ __global__ __launch_bounds__(kSortThreads) void cand_chunk_kernel(Seg seg, uint4
 }
 
 template <class Seg>
-__global__ __launch_bounds__(256) void cand_rank_kernel(Seg seg, const uint4* cand, int64_t cap) {
+__global__ __launch_bounds__(256) void cand_rank_kernel(Seg seg, const uint4* cand, int64_t cap, int64_t limit) {
   const int q = blockIdx.y;
   const WuDev& w = seg.unit(q);
   if (!w.cand || w.top_k <= 0) return;
   const int64_t n = cand_held(w, cap);
-  if (n <= kSortChunk) return;                     // complete
+  if (n <= kSortChunk || n > limit) return;        // complete, or sorted as a whole
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i == 0) *w.n_above = *w.cand_count;
   if (i >= n) {
@@ -1699,27 +1707,36 @@ __global__ __launch_bounds__(256) void cand_rank_kernel(Seg seg, const uint4* ca
   if (rank < w.top_k) w.top[rank] = top_entry(w, me);
 }
 
-// Toplists of more than kRankTopK entries, whose ranks would not be given up
-// early: a bitonic sort of every segment, then its first top_k entries.  Slots
-// past a segment's count become sentinels that rank last.
+// The segments that hold more than `over` entries: a bitonic sort of the whole
+// segment, then its first top_k entries.  Slots past a segment's count become
+// sentinels that rank last.  Also the path of toplists of more than kRankTopK
+// entries, whose ranks would not be given up early (over = -1).
 constexpr int kRankTopK = 65536;
 
 template <class Seg>
-__global__ __launch_bounds__(256) void cand_pad_kernel(Seg seg, uint4* cand, int64_t cap, int64_t total) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const int q = (int)(i / cap);
+__device__ __forceinline__ bool sorts_whole(const Seg& seg, int q, int64_t cap, int64_t over) {
   const WuDev& w = seg.unit(q);
-  const int64_t n = w.cand_count ? cand_held(w, cap) : 0;
-  if ((i & (cap - 1)) >= n) cand[i] = make_uint4(__float_as_uint(-__builtin_huge_valf()), 0u, ~0u, ~0u);
+  return w.cand && w.top_k > 0 && cand_held(w, cap) > over;
 }
 
-// One compare-exchange pass of a bitonic sort of every cap-long segment
-// (pass (k, j), j < k <= cap): best-ranked first when k reaches cap.
-__global__ __launch_bounds__(256) void cand_sort_pass_kernel(uint4* cand, int64_t total, int64_t cap, int64_t k,
-                                                             int64_t j) {
+template <class Seg>
+__global__ __launch_bounds__(256) void cand_pad_kernel(Seg seg, uint4* cand, int lg_cap, int64_t total, int64_t over) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
+  const int64_t cap = (int64_t)1 << lg_cap;
+  const int q = (int)(i >> lg_cap);
+  if (i >= total || !sorts_whole(seg, q, cap, over)) return;
+  if ((i & (cap - 1)) >= cand_held(seg.unit(q), cap))
+    cand[i] = make_uint4(__float_as_uint(-__builtin_huge_valf()), 0u, ~0u, ~0u);
+}
+
+// One compare-exchange pass of a bitonic sort of the cap-long segments
+// (pass (k, j), j < k <= cap): best-ranked first when k reaches cap.
+template <class Seg>
+__global__ __launch_bounds__(256) void cand_sort_pass_kernel(Seg seg, uint4* cand, int lg_cap, int64_t total,
+                                                             int64_t over, int64_t k, int64_t j) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t cap = (int64_t)1 << lg_cap;
+  if (i >= total || !sorts_whole(seg, (int)(i >> lg_cap), cap, over)) return;
   const int64_t p = i ^ j;
   if (p <= i) return;
   const bool first_best = ((i & (cap - 1)) & k) == 0;
@@ -1733,10 +1750,10 @@ __global__ __launch_bounds__(256) void cand_sort_pass_kernel(uint4* cand, int64_
 // The first top_k entries of each sorted segment, decoded to (2F, sky, fdot,
 // f); entries past the count get indices -1.  Also publishes n_above.
 template <class Seg>
-__global__ __launch_bounds__(256) void top_write_kernel(Seg seg, const uint4* cand, int64_t cap) {
+__global__ __launch_bounds__(256) void top_write_kernel(Seg seg, const uint4* cand, int64_t cap, int64_t over) {
   const int q = blockIdx.y;
+  if (!sorts_whole(seg, q, cap, over)) return;
   const WuDev& w = seg.unit(q);
-  if (!w.cand || w.top_k <= 0) return;
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (t == 0) *w.n_above = *w.cand_count;
   if (t >= w.top_k) return;
@@ -2128,27 +2145,36 @@ static hipError_t top_select(const Seg& seg, int n_seg, uint4* cand, int64_t cap
   const int64_t total = (int64_t)n_seg * cap;
   if (n_seg <= 0 || cap <= 0 || (cap & (cap - 1)) != 0 || total / 256 + 1 > 0x7fffffffLL)
     return hipErrorInvalidConfiguration;
-  if (max_top_k <= kRankTopK) {
-    if (max_top_k <= 0) return hipSuccess;
-    const dim3 chunks((unsigned)((cap + kSortChunk - 1) / kSortChunk), (unsigned)n_seg);
-    hipLaunchKernelGGL(cand_chunk_kernel<Seg>, chunks, dim3(kSortThreads), 0, st, seg, cand, cap);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || cap <= kSortChunk) return e;
-    const dim3 entries((unsigned)((cap + 255) / 256), (unsigned)n_seg);
-    hipLaunchKernelGGL(cand_rank_kernel<Seg>, entries, dim3(256), 0, st, seg, (const uint4*)cand, cap);
-    return hipGetLastError();
+  if (max_top_k <= 0) return hipSuccess;
+  const int64_t over = max_top_k > kRankTopK                                          ? -1
+                       : cap <= kRankHeld || (cap <= kRankCap && max_top_k <= kRankShort) ? cap
+                                                                                      : kRankHeld;
+  hipError_t e = hipSuccess;
+  if (over > 0) {                                  // segments that hold at most `over`
+    const dim3 chunks((unsigned)((over + kSortChunk - 1) / kSortChunk), (unsigned)n_seg);
+    hipLaunchKernelGGL(cand_chunk_kernel<Seg>, chunks, dim3(kSortThreads), 0, st, seg, cand, cap, over);
+    e = hipGetLastError();
+    if (e == hipSuccess && over > kSortChunk) {
+      const dim3 entries((unsigned)((over + 255) / 256), (unsigned)n_seg);
+      hipLaunchKernelGGL(cand_rank_kernel<Seg>, entries, dim3(256), 0, st, seg, (const uint4*)cand, cap, over);
+      e = hipGetLastError();
+    }
+    if (over == cap) return e;
   }
+  const int lg_cap = __builtin_ctzll((unsigned long long)cap);
   const dim3 grid((unsigned)((total + 255) / 256)), block(256);
-  hipLaunchKernelGGL(cand_pad_kernel<Seg>, grid, block, 0, st, seg, cand, cap, total);
-  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(cand_pad_kernel<Seg>, grid, block, 0, st, seg, cand, lg_cap, total, over);
+    e = hipGetLastError();
+  }
   for (int64_t k = 2; k <= cap && e == hipSuccess; k <<= 1)
     for (int64_t j = k >> 1; j > 0 && e == hipSuccess; j >>= 1) {
-      hipLaunchKernelGGL(cand_sort_pass_kernel, grid, block, 0, st, cand, total, cap, k, j);
+      hipLaunchKernelGGL(cand_sort_pass_kernel<Seg>, grid, block, 0, st, seg, cand, lg_cap, total, over, k, j);
       e = hipGetLastError();
     }
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(top_write_kernel<Seg>, dim3((unsigned)((max_top_k + 255) / 256), (unsigned)n_seg), block, 0, st,
-                     seg, (const uint4*)cand, cap);
+                     seg, (const uint4*)cand, cap, over);
   return hipGetLastError();
 }
 
