@@ -7,10 +7,14 @@
 
 namespace fstat {
 
-// Sky points of a block at most.
+// Sky points of a block at most; with few SFTs (up to kFewSfts) kSkyChunkFew.
 constexpr int kSkyChunk = 64;
+constexpr int kSkyChunkFew = 256;
+constexpr int kFewSfts = 128;
 
-// A block takes 256 SFTs, one per thread, at up to kSkyChunk sky points.  Each
+// A block takes 256 SFTs, one per thread, at up to kSkyChunk sky points; of
+// few SFTs, the lanes of the next power of two take every (256 / lanes)-th of
+// its sky points (1 SFT x 1e6 points 66 us with one lane busy, so 14).  Each
 // thread forms r, v (sum of the orbital and the diurnal parts; written by the
 // first chunk's blocks) and the six unique components of its detector tensor
 // D = (u u^T - w w^T) / 2; the first threads form, per sky point, the wave
@@ -22,11 +26,13 @@ constexpr int kSkyChunk = 64;
 // The wave frame of n = (cos d cos al, cos d sin al, sin d) is formed from the
 // components directly: with rho = sqrt(nx^2 + ny^2), X = (ny, -nx, 0) / rho,
 // Y = (-nz nx / rho, -nz ny / rho, rho); at the poles (rho = 0) al = 0.
+template <bool FEW>
 __global__ __launch_bounds__(256) void detector_kernel(EarthModel m, int64_t n_sft, const double* t_mid,
                                                        const int32_t* site_of_sft, int64_t n_sky, const double* sky,
-                                                       int chunk, double* pos, double* vel, float* a, float* b) {
-  __shared__ double form[kSkyChunk][12];
-  const int64_t n_sb = (n_sft + 255) / 256;
+                                                       int chunk, int lg_lanes, double* pos, double* vel, float* a,
+                                                       float* b) {
+  __shared__ double form[FEW ? kSkyChunkFew : kSkyChunk][12];
+  const int64_t n_sb = FEW ? 1 : (n_sft + 255) / 256;
   const int64_t sb = blockIdx.x % n_sb, kb = blockIdx.x / n_sb;
   const int64_t s0 = kb * chunk;
   const int ns = (int)(n_sky - s0 < chunk ? n_sky - s0 : chunk);
@@ -52,7 +58,9 @@ __global__ __launch_bounds__(256) void detector_kernel(EarthModel m, int64_t n_s
       f[6 + c] = c < 3 ? 2.0 * (X[p[c]] * Y[q[c]]) : 2.0 * (X[p[c]] * Y[q[c]] + X[q[c]] * Y[p[c]]);
     }
   }
-  const int64_t al = sb * 256 + tid;
+  const int lane = FEW ? tid & ((1 << lg_lanes) - 1) : tid, group = FEW ? tid >> lg_lanes : 0;
+  const int groups = FEW ? 256 >> lg_lanes : 1;
+  const int64_t al = sb * 256 + lane;
   const bool live = al < n_sft;
   double d[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   if (live) {
@@ -63,7 +71,7 @@ __global__ __launch_bounds__(256) void detector_kernel(EarthModel m, int64_t n_s
     double sp, cp, sth, cth;
     sincos(m.orbit_phase + m.orbit_rate * dt, &sp, &cp);
     sincos(st.lon + m.sidereal_phase + m.sidereal_rate * dt, &sth, &cth);
-    if (kb == 0) {
+    if (kb == 0 && group == 0) {
       const double nan = __builtin_nan("");
       const double R = m.orbit_radius, RW = m.orbit_radius * m.orbit_rate;
       const double Re = m.earth_radius, ReW = m.earth_radius * m.sidereal_rate;
@@ -93,7 +101,7 @@ __global__ __launch_bounds__(256) void detector_kernel(EarthModel m, int64_t n_s
   }
   __syncthreads();
   if (!live) return;
-  for (int s = 0; s < ns; ++s) {
+  for (int s = group; s < ns; s += groups) {
     const double* f = form[s];
     double x = d[0] * f[0], y = d[0] * f[6];
 #pragma unroll
@@ -113,12 +121,21 @@ hipError_t launch_detector_inputs(const EarthModel& m, int64_t n_sft, const doub
   // sky points per block: enough blocks to fill the device first (about four
   // per CU), then as many points per block as share its tensors
   const int64_t n_sb = (n_sft + 255) / 256;
+  const bool few = n_sft <= kFewSfts;
+  const int64_t most = few ? kSkyChunkFew : kSkyChunk;
   int64_t chunk = (n_sky * n_sb + 1023) / 1024;
-  chunk = chunk < 1 ? 1 : (chunk > kSkyChunk ? kSkyChunk : chunk);
+  chunk = chunk < 1 ? 1 : (chunk > most ? most : chunk);
+  int lg_lanes = 8;
+  if (few) {
+    for (lg_lanes = 0; (1 << lg_lanes) < n_sft; ++lg_lanes) {
+    }
+    const int64_t groups = 256 >> lg_lanes;        // every group of lanes has a sky point
+    chunk = (chunk + groups - 1) / groups * groups;
+  }
   const int64_t blocks = n_sb * ((n_sky + chunk - 1) / chunk);
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(detector_kernel, dim3((unsigned)blocks), dim3(256), 0, st, m, n_sft, t_mid, site_of_sft, n_sky,
-                     sky, (int)chunk, pos, vel, a, b);
+  hipLaunchKernelGGL(few ? detector_kernel<true> : detector_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, m,
+                     n_sft, t_mid, site_of_sft, n_sky, sky, (int)chunk, lg_lanes, pos, vel, a, b);
   return hipGetLastError();
 }
 
