@@ -199,30 +199,32 @@ int fstat_plan_create(fstat_plan** out, const fstat_desc* d);
  * call waits for this check and returns FSTAT_E_BAND (no output written: at
  * most the coefficient pass, into the plan's scratch, and a demodulation that
  * finds the check failed and ends were queued) if it fails; (2) the
- * demodulation kernel, which writes `out` asynchronously.  Between the two, the interp kernel's host side copies the
- * sky vectors back (one more short wait) to pair neighbouring sky points
- * into tiles of two where the slice can hold both (fstat_last_tile reports
- * the shape that ran).  Returns after (2) is enqueued.  A stream under capture
- * is refused (FSTAT_E_DEVICE, nothing queued; so by every call that waits for
- * a band check): the check would be made only when the graph runs. */
+ * demodulation kernel, which writes `out` asynchronously.  With the interp
+ * kernel the check brings the sky vectors back, and the host pairs neighbouring
+ * sky points into tiles of two where the slice can hold both and the pairs fill
+ * the device (fstat_last_tile reports the shape that ran).  Returns after (2) is
+ * enqueued; a call that fails returns once nothing that it queued is under way.
+ * A stream under capture is refused (FSTAT_E_DEVICE, nothing queued; so by
+ * every call that waits for a band check): the check would be made only when
+ * the graph runs. */
 int fstat_compute(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void* stream);
 
-/* fstat_compute for callers that cannot allocate device memory (while
- * another stream is under capture, tight serving loops, harnesses that forbid hipMalloc): the
- * same kernels and results as fstat_compute on the same plan, with every
- * piece of device scratch (geometry, coefficients, toplist buffer; the status
- * record of 56 bytes is made with the plan) in one static device array of FSTAT_NOALLOC_SCRATCH_BYTES that
- * each GPU using the library holds until the process ends.  The call itself
- * allocates nothing, device or pinned; create the plan beforehand.  The work
- * unit must fit the array: about 16 B per (sky point, SFT) plus, for the
- * interp kernel, 64 B per (SFT, bin) (32 B with FSTAT_FLAG_COEF16) must stay
- * within FSTAT_NOALLOC_SCRATCH_BYTES less 2 MiB + 4 KiB (the tables and
- * the toplist buffer), and top_k within 65536;
- * otherwise FSTAT_E_SIZE with the sizes in fstat_last_error, before anything
- * is launched.  Every call on one GPU shares that GPU's array: calls that
- * overlap in time on one GPU (other threads, other streams, other plans) race
- * and give wrong results; serialise them.  Inputs, outputs, errors and the
- * wait for the band check are as for fstat_compute. */
+/* fstat_compute for callers that cannot allocate device memory (while another
+ * stream is under capture, tight serving loops, harnesses that forbid
+ * hipMalloc): the same kernels and results as fstat_compute on the same plan,
+ * with every piece of device scratch (geometry, coefficients, toplist buffer;
+ * the status record of 56 bytes is made with the plan) in one static device
+ * array of FSTAT_NOALLOC_SCRATCH_BYTES that each GPU using the library holds
+ * until the process ends.  The call itself allocates nothing, device or pinned;
+ * create the plan beforehand.  The work unit must fit the array: about 16 B per
+ * (sky point, SFT) plus, for the interp kernel, 64 B per (SFT, bin) (32 B with
+ * FSTAT_FLAG_COEF16) must stay within FSTAT_NOALLOC_SCRATCH_BYTES less 2 MiB +
+ * 4 KiB (the tables and the toplist buffer), and top_k within 65536; otherwise
+ * FSTAT_E_SIZE with the sizes in fstat_last_error, before anything is launched.
+ * Every call on one GPU shares that GPU's array: calls that overlap in time on
+ * one GPU (other threads, other streams, other plans) race and give wrong
+ * results; serialise them.  Inputs, outputs, errors and the wait for the band
+ * check are as for fstat_compute. */
 #define FSTAT_NOALLOC_SCRATCH_BYTES (128u << 20)
 int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* out, void* stream);
 
@@ -234,13 +236,12 @@ int fstat_compute_noalloc(fstat_plan* p, const fstat_wu* wu, const fstat_out* ou
  * per unit to waste the fewest lanes weighted by the measured cost of each
  * size (5 spindowns run as one block of 5, 12 as 6 + 6, 32 as 16 + 16); the
  * blocks of at most 8 take tiles of two neighbouring sky points where the
- * unit's sky grid allows (FP32 coefficients; the host reads the sky vectors
- * back once per group to pair them).  Per block of SFTs (256 unless fstat_autotune chose
- * another) one persistent launch per spindown-block size runs over the units
+ * unit's sky grid allows and few points go without a partner (FP32
+ * coefficients; the sky vectors come back with the group's band check).  Per
+ * block of SFTs (256 unless fstat_autotune chose another) one persistent launch per spindown-block size runs over the units
  * with SFTs left; inside a launch the tiles are dealt to one queue per XCD in
  * chunks of consecutive tiles, so that tiles sharing coefficients are served
- * by one L2.  All
- * work units are validated and band-checked before any output is written (the
+ * by one L2.  All work units are validated and band-checked before any output is written (the
  * coefficient passes, which write only scratch, run meanwhile); on
  * failure the index of the first failing work unit is in fstat_last_error.
  * The demodulation's launch sequence is captured once in a hipGraph per
@@ -315,7 +316,8 @@ int fstat_detector_inputs(fstat_plan* p, const fstat_earth* earth, int32_t n_sit
  * waves per SIMD (interp) or SFTs per LDS chunk (direct), SFTs per
  * launch with 0 = all, work-group size of the interp kernel; "1 1 0 64" leaves
  * the choice between one wave per (sky point, spindown, 64 frequencies) and
- * the default tile to the library, per unit, as without tuning.  Batch classes
+ * the default tile to the library, per unit, as without tuning; any other line
+ * is the shape of every unit of its class, whatever its size.  Batch classes
  * ("batch_s<storage>_c<coef16>"): spindowns per thread (8: blocks of 16 and
  * 4 to 8 split per unit as fstat_batch_compute describes; 4: blocks of 4 only),
  * tiles per chunk of the per-XCD queues, SFTs per launch (0 = all), 256.

@@ -1473,9 +1473,10 @@ int batch_chains(fstat_plan* p) {
 }
 
 // Batched interp path: work units are grouped so that one group's scratch
-// (geometry, A,B,C, coefficients) fits the budget; per group the geometry is
-// computed and checked, the work-unit table is uploaded, and the coefficient
-// pass plus the persistent demodulation kernel run as one captured graph.
+// (geometry, A,B,C, coefficients) fits the budget; per group the geometry and
+// the coefficient passes are queued, then, the check read and the sky points
+// paired, the demodulation tables are uploaded and the persistent kernels and
+// toplist selections run as one captured graph.
 int batch_interp(fstat_plan* p, const fstat_wu* wus, int n, const fstat_out* outs, hipStream_t st) {
   const Tile bt = batch_tile(p);
   int64_t max_sft = 1;
