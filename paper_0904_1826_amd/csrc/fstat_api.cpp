@@ -1162,16 +1162,18 @@ bool wave_beats_tile(const fstat_plan* p, const fstat_wu* wu, bool paired);
 // frequencies; paired, single): 8: 1000 sky points 10.29, 10.63 ms and (step
 // 0.5 bins) 11.48, 11.69; 600 with 318 and 316 tiles 6.72, 6.51 and 7.34, 7.12;
 // 7: 1000 points 9.23, 9.68 and 10.34, 10.79; 6: 8.21, 8.84 and 9.26, 9.66; 5:
-// 7.31, 8.03 and 7.98, 8.84; 4: 6.07, 7.57 and 6.43, 7.75.  So pairs pay if few
-// points go without a partner.
+// 7.31, 8.03 and 7.98, 8.84; 4: 6.07, 7.57 and 6.43, 7.75.
 double pair_cost(int nfd, bool shared) {
   static const double kShared[] = {1.60, 1.82, 1.85, 1.90, 1.92}, kPlain[] = {1.65, 1.82, 1.91, 1.91, 1.95};
   const int i = (nfd < 4 ? 4 : nfd > 8 ? 8 : nfd) - 4;
   return shared ? kShared[i] : kPlain[i];
 }
-bool pairs_pay(int64_t np, const fstat_wu* wu, bool shared) {
-  return pair_cost((int)std::min<int64_t>(wu->n_fd, 8), shared) * (double)np <= (double)wu->n_sky;
-}
+
+// Whether a batched unit pairs: if few points go without a partner.  One line
+// for every block size (8 and, without shared coefficients, 5 spindowns), since
+// units that pair alike share a launch and its tail: with lines by block size 6
+// units of up to 800 x 8 x 1500 x 300 took 5.4 instead of 5.0 ms.
+bool pairs_pay(int64_t np, int64_t n, bool shared) { return (shared ? 1.91 : 1.80) * (double)np <= (double)n; }
 
 // Time of a completed tile's launches in the time of one (sky point, spindown)
 // slot on a full device: the work-groups run in rounds of `per` on each CU (256
@@ -1376,7 +1378,7 @@ int batch_unit_shapes(fstat_plan* p, const fstat_wu* wus, const std::vector<int>
     us[q].pair_width =
         make_pairs(&wus[k], p->bstat_h[k], p->sky_h + 3 * sky_off[k], p->pairs_h + sky_off[k], &us[q].n_pairs);
     if (us[q].pair_width &&
-        !pairs_pay(us[q].n_pairs, &wus[k], slots_share(&wus[k], status_tau(p->bstat_h[k]))))
+        !pairs_pay(us[q].n_pairs, wus[k].n_sky, slots_share(&wus[k], status_tau(p->bstat_h[k]))))
       us[q].pair_width = 0;
     if (!us[q].pair_width) continue;
     const hipError_t e = hipMemcpyAsync(p->pairs_d + sky_off[k], p->pairs_h + sky_off[k],
